@@ -518,13 +518,15 @@ int mag_invariant_count(const mag_tensor* tensor, int32_t* n_unfoldings, int64_t
  * exactly; MFMA products), reduced to tridiagonal form and bisected; an
  * eigenvalue is within about 1e-13 of the largest (relative), so a singular
  * value far below the largest carries an absolute error near 3e-7 of it.
- * Gram sides up to 512 are reduced by one workgroup each, all unfoldings side
- * by side, and their eigenvalues then bisected by waves spread over the whole
- * device (the workspace holds each tridiagonal form between the two); larger
- * ones (up to MAG_SVD_MAX_K) one after another, each
- * Householder step spread over the whole device (about 4 launches per row of
- * the Gram matrix, so a side of n costs some 4 n launches; the workspace then
- * also holds about (n / 256 + 4) n doubles of scratch).
+ * Gram sides up to 128 (up to 512 where a batch holds many) are reduced by one
+ * workgroup each, all unfoldings side by side; sides up to 4096 by groups of
+ * workgroups that keep the matrix on the chip and run all together
+ * (cooperative launches); larger ones (up to MAG_SVD_MAX_K) first take
+ * device-wide Householder steps, four launches each, down to 4096 (the
+ * workspace then also holds about (n / 256 + 3) n doubles of scratch).  The
+ * eigenvalues of all unfoldings are then bisected by waves spread over the
+ * whole device.  MAG_E_HIP also when the workgroups of a group lose touch (a
+ * member waited 20 s for another).
  * Synchronizes `stream`.  Errors: MAG_E_NULL, MAG_E_SIZE, MAG_E_ALIGN,
  * MAG_E_WORKSPACE, MAG_E_HIP.
  */

@@ -1905,11 +1905,17 @@ struct InvPlan {
     std::vector<int64_t> spec_off;
     int n_narrow = 0, n_whole = 0;
     int64_t gram_len = 0, n_items = 0, n_items_narrow = 0, n_items_whole = 0;
-    // eigenvalue work items (tasks with K <= mag::SVD_SMALL_K, in task order)
-    // and the doubles of their tridiagonal forms (2 K + 3 each)
-    int64_t n_eig_items = 0, tri_len = 0;
+    // eigenvalue work items (in task order, 64 / eig_lanes values each), the
+    // doubles of the tridiagonal forms, and the exchange words of the sides that
+    // a group of workgroups may reduce
+    int64_t n_eig_items = 0, tri_len = 0, n_words = 0;
+    int eig_lanes = 1;
     int large_k = 0;  // largest Gram side above mag::SVD_SMALL_K (0: none)
 };
+
+// the part of a Gram side that a group of workgroups reduces (a larger one is
+// first brought down to it)
+int group_side(int64_t K) { return (int)std::min<int64_t>(K, mag::SVD_GROUP_MAX); }
 
 int plan_invariants(const mag_tensor* ts, int32_t n, InvPlan& pl)
 {
@@ -1955,28 +1961,64 @@ int plan_invariants(const mag_tensor* ts, int32_t n, InvPlan& pl)
     pl.spec_off.insert(pl.spec_off.end(), whole_off.begin(), whole_off.end());
     pl.tasks.insert(pl.tasks.end(), wide.begin(), wide.end());
     pl.spec_off.insert(pl.spec_off.end(), wide_off.begin(), wide_off.end());
+    pl.eig_lanes = mag::sturm_lanes(so);
+    const int per = 64 / pl.eig_lanes;
     for (auto& t : pl.tasks) {
         t.eig0 = pl.n_eig_items;
-        if (t.K <= mag::SVD_SMALL_K) {
-            pl.n_eig_items += (t.K + mag::EIG_PER_ITEM - 1) / mag::EIG_PER_ITEM;
-            pl.tri_len += 2 * t.K + 3;
-        }
+        pl.n_eig_items += (t.K + per - 1) / per;
+        pl.tri_len += mag::tri_len((int)t.K);
+        if (t.K >= mag::SVD_GROUP_MIN) pl.n_words += mag::tri_group_words(group_side(t.K));
     }
     return MAG_OK;
 }
 
-size_t carve_invariants(const InvPlan& pl, void* ws, mag::SvdTask** tasks, double** gram,
-                        double** tri, double** large)
+struct InvWorkspace {
+    mag::SvdTask* tasks;
+    double* gram;     // the matrices, and right behind them the exchange words
+    uint64_t* words;  // (n_words, then one word: a group lost touch)
+    double* tri;
+    double* large;
+    int64_t clear_len;  // doubles from gram on that start at zero
+};
+
+size_t carve_invariants(const InvPlan& pl, void* ws, InvWorkspace& w)
 {
     Carver c;
     c.base = static_cast<char*>(ws);
-    *tasks = c.take<mag::SvdTask>(std::max<size_t>(pl.tasks.size(), 1));
-    *gram = c.take<double>((size_t)std::max<int64_t>(pl.gram_len, 1));
-    *tri = c.take<double>((size_t)std::max<int64_t>(pl.tri_len, 1));
-    // scratch of the many-workgroup reduction, shared by the large unfoldings
-    // (they run one after another)
-    *large = pl.large_k ? c.take<double>((size_t)mag::svd_large_scratch(pl.large_k)) : nullptr;
+    w.tasks = c.take<mag::SvdTask>(std::max<size_t>(pl.tasks.size(), 1));
+    w.clear_len = pl.gram_len + pl.n_words + 1;
+    w.gram = c.take<double>((size_t)w.clear_len);
+    w.words = w.gram ? reinterpret_cast<uint64_t*>(w.gram + pl.gram_len) : nullptr;
+    w.tri = c.take<double>((size_t)std::max<int64_t>(pl.tri_len, 1));
+    // scratch of the device-wide reduction steps, shared by the unfoldings that
+    // take them (they run one after another)
+    w.large = pl.large_k ? c.take<double>((size_t)mag::svd_large_scratch(pl.large_k)) : nullptr;
     return c.off;
+}
+
+// the largest Gram side that one workgroup reduces in this call (the larger
+// ones take groups of workgroups).  Sides up to 128 are reduced in LDS; above,
+// one workgroup per matrix works from L2, about 4 + 39 (K / 512)^2 us a step
+// (measured: 21.9 ms at K = 512), up to one matrix per CU at a time; a group
+// takes about 3.3 us a step whatever the side (1.67 ms at K = 512), but only as
+// many matrices at a time as have room (launch rounds)
+int eig_side(const InvPlan& pl)
+{
+    std::vector<int> mid;  // in the order in which the groups would be launched
+    int kmax = 0;
+    for (const auto& t : pl.tasks)
+        if (t.K >= mag::SVD_GROUP_MIN && t.K <= mag::SVD_SMALL_K) {
+            mid.push_back((int)t.K);
+            kmax = std::max(kmax, (int)t.K);
+        }
+    if (mid.empty()) return mag::SVD_SMALL_K;
+    for (int k : mid)
+        if (!mag::tri_group_fits(k)) return mag::SVD_SMALL_K;
+    std::sort(mid.begin(), mid.end(), [](int a, int b) { return a > b; });
+    const double r = (double)kmax / 512.0;
+    const double one = (4.0 + 39.0 * r * r) * (double)((mid.size() + 255) / 256);
+    const double group = 3.3 * (double)mag::tri_group_rounds(mid.data(), (int)mid.size());
+    return group < one ? mag::SVD_GROUP_MIN - 1 : mag::SVD_SMALL_K;
 }
 
 // spectra descriptors of a tensor set: offsets in the order mag_invariants writes
@@ -2019,9 +2061,8 @@ int mag_invariants_workspace_size(const mag_tensor* tensors, int32_t n_tensors, 
     InvPlan pl;
     int rc = plan_invariants(tensors, n_tensors, pl);
     if (rc) return rc;
-    mag::SvdTask* t;
-    double *g, *tr, *lg;
-    *bytes = carve_invariants(pl, nullptr, &t, &g, &tr, &lg);
+    InvWorkspace w;
+    *bytes = carve_invariants(pl, nullptr, w);
     return MAG_OK;
 }
 
@@ -2041,37 +2082,66 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
     if (!aligned(spectra, 8)) return fail(MAG_E_ALIGN, "spectra not 8-byte aligned");
     if (!workspace) return fail(MAG_E_NULL, "workspace is NULL");
     if (!aligned(workspace, 256)) return fail(MAG_E_WORKSPACE, "workspace must be 256-byte aligned");
-    mag::SvdTask* dtasks;
-    double *gram, *tri, *large;
-    const size_t need = carve_invariants(pl, nullptr, &dtasks, &gram, &tri, &large);
+    InvWorkspace w;
+    const size_t need = carve_invariants(pl, nullptr, w);
     if (workspace_bytes < need) return fail(MAG_E_WORKSPACE, "workspace too small");
-    carve_invariants(pl, workspace, &dtasks, &gram, &tri, &large);
-    int64_t go = 0, to = 0;
+    carve_invariants(pl, workspace, w);
+    int64_t go = 0, to = 0, wo = 0;
+    const int eig_max = eig_side(pl);
+    bool any_eig = false;
+    std::vector<mag::TriMatrix> groups;
     for (size_t i = 0; i < pl.tasks.size(); ++i) {
         mag::SvdTask& t = pl.tasks[i];
-        t.gram = gram + go;
+        const int K = (int)t.K;
+        t.gram = w.gram + go;
         t.out = spectra + pl.spec_off[i];
         go += t.K * t.K;
-        t.tri = nullptr;
-        if (t.K <= mag::SVD_SMALL_K) {
-            t.tri = tri + to;
-            to += 2 * t.K + 3;
-        }
+        t.tri = w.tri + to;
+        to += mag::tri_len(K);
+        any_eig = any_eig || K <= eig_max;
+        if (K < mag::SVD_GROUP_MIN) continue;
+        const int side = group_side(K), k0 = K - side;
+        if (K > eig_max && mag::tri_group_fits(side))
+            groups.push_back(mag::TriMatrix{t.gram + (size_t)k0 * K + k0, t.tri + k0,
+                                            t.tri + K + k0, w.words + wo, K, side, 0u});
+        wo += mag::tri_group_words(side);
     }
+    std::sort(groups.begin(), groups.end(),
+              [](const mag::TriMatrix& a, const mag::TriMatrix& b) { return a.n > b.n; });
+    int32_t* failed = reinterpret_cast<int32_t*>(w.words + pl.n_words);
     hipError_t e;
-    if ((e = hipMemcpyAsync(dtasks, pl.tasks.data(), sizeof(mag::SvdTask) * pl.tasks.size(),
+    if ((e = hipMemcpyAsync(w.tasks, pl.tasks.data(), sizeof(mag::SvdTask) * pl.tasks.size(),
                             hipMemcpyHostToDevice, stream)) != hipSuccess)
         return hip_fail(e, "task copy");
-    if ((e = mag::launch_svd(dtasks, (int)pl.tasks.size(), pl.n_narrow, pl.n_items_narrow,
-                             pl.n_whole, pl.n_items_whole, pl.n_items, pl.n_eig_items, gram,
-                             pl.gram_len, stream)) != hipSuccess)
+    if ((e = mag::launch_svd(w.tasks, (int)pl.tasks.size(), pl.n_narrow, pl.n_items_narrow,
+                             pl.n_whole, pl.n_items_whole, pl.n_items, any_eig ? eig_max : 0,
+                             w.gram, w.clear_len, stream)) != hipSuccess)
         return hip_fail(e, "invariant kernels");
-    for (const auto& t : pl.tasks)
-        if (t.K > mag::SVD_SMALL_K &&
-            (e = mag::launch_svd_large(t.gram, (int)t.K, large, t.out, stream)) != hipSuccess)
+    // sides beyond the groups' reach: device-wide steps down to it (or, on a
+    // device with too few CUs for the group, all the way)
+    for (const auto& t : pl.tasks) {
+        if (t.K <= eig_max) continue;
+        const int K = (int)t.K, side = group_side(K);
+        const int stop = mag::tri_group_fits(side) ? K - side : K - 2;
+        if (stop > 0 && (e = mag::launch_svd_large(t.gram, K, stop, w.large, t.tri, t.tri + K,
+                                                   stream)) != hipSuccess)
             return hip_fail(e, "large unfolding kernels");
+    }
+    int32_t lost = 0;
+    if (!groups.empty()) {
+        if ((e = mag::launch_tri_groups(groups.data(), (int)groups.size(), failed, stream)) !=
+            hipSuccess)
+            return hip_fail(e, "reduction kernels");
+        if ((e = hipMemcpyAsync(&lost, failed, sizeof(lost), hipMemcpyDeviceToHost, stream)) !=
+            hipSuccess)
+            return hip_fail(e, "status copy");
+    }
+    if ((e = mag::launch_sturm(w.tasks, (int)pl.tasks.size(), pl.n_eig_items, pl.eig_lanes,
+                               stream)) != hipSuccess)
+        return hip_fail(e, "eigenvalue kernels");
     // (the task table on the host stays alive until the copy is done)
     if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "synchronize");
+    if (lost) return fail(MAG_E_HIP, "the workgroups of a reduction lost touch");
     return MAG_OK;
 }
 

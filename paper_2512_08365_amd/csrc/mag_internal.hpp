@@ -271,7 +271,8 @@ constexpr int SVD_MAX_UNF = 15;       // unfoldings of a rank-5 tensor, compleme
 constexpr int64_t GRAM_CHUNK = 2048;  // unfolding columns per Gram work item
 constexpr int64_t GRAM_CHUNK_NARROW = 1024;  // the same for K <= GRAM_NARROW (one 32-side block)
 constexpr int GRAM_NARROW = 32;       // Gram sides up to this use 32-side blocks (else 64)
-constexpr int EIG_PER_ITEM = 16;      // eigenvalues per work item of the Sturm counts
+constexpr int SVD_GROUP_MIN = 129;    // Gram sides that a group of workgroups can reduce
+constexpr int SVD_GROUP_MAX = 4096;
 constexpr int GRAM_WHOLE = 128;       // sides in (64, GRAM_WHOLE]: the whole triangle per item
 constexpr int64_t GRAM_CHUNK_WHOLE = 1024;  // unfolding columns per item for those sides
 
@@ -284,8 +285,8 @@ struct SvdTask {
     double* gram;    // [K][K]
     double* out;     // [K] singular values, descending
     int64_t item0;   // first Gram work item of this task (within its block size's launch)
-    double* tri;     // (K <= SVD_SMALL_K) the tridiagonal form: d[K], e2[K], glo, ghi, pivmin
-    int64_t eig0;    // (K <= SVD_SMALL_K) first eigenvalue work item, EIG_PER_ITEM values each
+    double* tri;     // the tridiagonal form: d[K], e2[K], then as the counts read it (tri_len)
+    int64_t eig0;    // first eigenvalue work item (one wave's eigenvalues each)
     int32_t nt;      // row blocks: 1 when K <= GRAM_NARROW or 64 < K <= GRAM_WHOLE, else ceil(K / 64)
     int32_t nchunk;  // column chunks of L: GRAM_CHUNK_NARROW, GRAM_CHUNK_WHOLE or GRAM_CHUNK columns
 };
@@ -298,20 +299,78 @@ struct SpecDesc {
     int64_t len[SVD_MAX_UNF];
 };
 
-// Gram matrices (zeroed, then accumulated), then the spectra of the tasks
-// with K <= SVD_SMALL_K; the first n_narrow tasks (K <= GRAM_NARROW) are
-// numbered by their own n_items_narrow work items, the next n_whole (64 < K <=
-// GRAM_WHOLE) by n_items_whole, the others by n_items; the eigenvalue counts
-// by n_eig_items (each task's from its eig0, in task order)
+// a tridiagonal form's place: d, squared off-diagonals, then tri_padded(K) + 8
+// pairs {d_i, e2_{i-1}} scaled for the counts (the last 8 only read ahead),
+// the scaled bounds of the eigenvalues and the scale
+__host__ __device__ inline int tri_padded(int n) { return (n + 7) / 8 * 8; }
+__host__ __device__ inline double2* tri_pairs(double* tri, int n)
+{
+    return reinterpret_cast<double2*>(tri + 2 * tri_padded(n));
+}
+__host__ __device__ inline double* tri_bounds(double* tri, int n)
+{
+    return tri + 4 * tri_padded(n) + 16;
+}
+__host__ __device__ inline int64_t tri_len(int n) { return 4 * (int64_t)tri_padded(n) + 24; }
+
+// Gram matrices and exchange words (clear_len doubles, zeroed; the matrices
+// then accumulated), and the tridiagonal forms of the tasks with K <= eig_max;
+// the first n_narrow tasks (K <= GRAM_NARROW) are numbered by their own
+// n_items_narrow work items, the next n_whole (64 < K <= GRAM_WHOLE) by
+// n_items_whole, the others by n_items
 hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n_items_narrow,
-                      int n_whole, int64_t n_items_whole, int64_t n_items, int64_t n_eig_items,
-                      double* gram, int64_t gram_len, hipStream_t stream);
-// the spectrum of one n x n Gram matrix with n > SVD_SMALL_K (overwritten):
-// a Householder step is four launches over the whole device, then
-// multisection on Sturm counts; scratch of svd_large_scratch(n) doubles
+                      int n_whole, int64_t n_items_whole, int64_t n_items, int eig_max,
+                      double* gram, int64_t clear_len, hipStream_t stream);
+
+// one symmetric matrix (both triangles, row stride lda, overwritten) and where
+// its tridiagonal form goes; words: tri_group_words(n) zeroed 64-bit words
+struct TriMatrix {
+    double* A;
+    double* d;
+    double* e2;
+    uint64_t* words;
+    int64_t lda;
+    int n;
+    uint32_t tag;  // step numbers used so far (0)
+};
+inline int64_t tri_group_words(int n)
+{
+    // two steps' words: two per double, two doubles a slot, and the members' parts
+    return 8 * (int64_t)((n <= 1024 ? 1024 : n <= 2048 ? 2048 : n <= 3072 ? 3072 : 4096) + 128);
+}
+struct TriGroupJob {
+    double* A;
+    double* d;
+    double* e2;
+    uint64_t* words;
+    int64_t lda;
+    int32_t n, G, wg0, slots, rows, n_mem, n_lds;
+    int32_t stop;   // steps to make (n - 2: all)
+    uint32_t tag0;  // step numbers used before
+};
+constexpr int TRI_GROUP_JOBS = 36;  // (the jobs travel as kernel arguments)
+struct TriGroupJobs {
+    int32_t count;
+    TriGroupJob job[TRI_GROUP_JOBS];
+};
+// whether a group of workgroups can reduce side n on this device; the launches
+// that a batch takes (matrices of one class side by side while they fit)
+bool tri_group_fits(int n);
+int tri_group_rounds(const int* n, int count);
+// tridiagonal forms by groups of workgroups (m is used up); *failed (zeroed)
+// becomes nonzero if members lost touch
+hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream_t stream);
+// Householder steps 0 .. stop - 1 of one n x n matrix, each four launches over
+// the whole device (stop = n - 2: the whole reduction, with the last corner);
+// scratch of svd_large_scratch(n) doubles
 int64_t svd_large_scratch(int n);
-hipError_t launch_svd_large(double* gram, int n, double* scratch, double* out,
+hipError_t launch_svd_large(double* gram, int n, int stop, double* scratch, double* d, double* e2,
                             hipStream_t stream);
+// every eigenvalue of the tasks' tridiagonal forms: G lanes each, n_items
+// waves of 64 / G eigenvalues; sigma = sqrt(max(lambda, 0)), descending
+int sturm_lanes(int64_t values);
+hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G,
+                        hipStream_t stream);
 // match[i * nb + j] = 1 when tensor i of A and tensor j of B have matching invariants
 hipError_t launch_svd_match(const SpecDesc* da, int na, const double* sa, const SpecDesc* db,
                             int nb, const double* sb, double eps, uint8_t* match,

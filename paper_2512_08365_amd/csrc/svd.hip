@@ -16,10 +16,8 @@
 //   sides in (64, 128]: k_gram_whole, the whole triangle per workgroup.
 // k_svd_eig: one workgroup per task: Householder reduction of the Gram
 //   matrix (in LDS up to side 128, else in place in global memory) to
-//   tridiagonal form and its Gershgorin bounds; k_svd_count: every
-//   eigenvalue by multisection on Sturm counts (the count of eigenvalues
-//   below x), a wave per 16 eigenvalues, sigma = sqrt(max(lambda, 0)),
-//   written in descending order.
+//   tridiagonal form; larger matrices take groups of workgroups, and every
+//   form's eigenvalues come from Sturm counts (tridiag.hip).
 // k_svd_match: one workgroup per tensor pair: which spectra of the two lists
 //   are close, then a one-to-one pairing by augmenting paths.
 
@@ -427,18 +425,6 @@ __device__ double block_sum(double v, double (*red)[EIG_THREADS / 64], int& flip
     return s;
 }
 
-// 1/q to a relative error of about 2^-48: the hardware estimate (measured on
-// gfx950 to 2^-24.4 over 4M values spanning 2^+-300) refined by one Newton
-// step, which squares its error.  The Sturm recurrence is a chain of these; a
-// correctly rounded division would lengthen every link, and a count computed
-// with this reciprocal is exact for the tridiagonal matrix with each e2[i]
-// perturbed by about 2^-48 relative, far below the bisection's own tolerance
-__device__ __forceinline__ double recip_nr(double q)
-{
-    const double r = __builtin_amdgcn_rcp(q);
-    return fma(r, fma(-q, r, 1.0), r);
-}
-
 constexpr int EIG_LDS_K = 128;  // Gram matrices up to this side are reduced in LDS
 
 // Householder reduction of the symmetric n x n matrix A (row stride n) to
@@ -554,91 +540,7 @@ __device__ void tridiagonalize(Ptr A, int n, double* v, double2* uw, double* wp,
     __syncthreads();
 }
 
-// Gershgorin interval of the symmetric tridiagonal matrix (d, e2), widened
-// by two ulps of its span and the smallest pivot allowed in a Sturm count
-template <class Ptr>
-__device__ void gershgorin(Ptr d, Ptr e2, int n, double& glo, double& ghi, double& pivmin)
-{
-    glo = INFINITY;
-    ghi = -INFINITY;
-    double emax = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double r = (i > 0 ? sqrt(e2[i - 1]) : 0.0) + (i + 1 < n ? sqrt(e2[i]) : 0.0);
-        glo = fmin(glo, d[i] - r);
-        ghi = fmax(ghi, d[i] + r);
-        if (i + 1 < n) emax = fmax(emax, e2[i]);
-    }
-    const double span = fmax(fabs(glo), fabs(ghi));
-    pivmin = 0x1p-1000 * fmax(1.0, emax);
-    glo -= 2.0 * DBL_EPSILON * span + pivmin;
-    ghi += 2.0 * DBL_EPSILON * span + pivmin;
-}
-
-// the k-th smallest eigenvalue of (d, e2) by multisection on Sturm counts
-// (count(lo) <= k < count(hi)): the G neighbouring threads of eigenvalue k
-// (g = 0 .. G-1, G a power of two dividing 64) each count at NC of a
-// round's NC G interior points, NC independent chains side by side, and the
-// round keeps the one of the interval's NC G + 1 parts that holds the
-// eigenvalue (the group agrees on lo and hi after every round)
-template <int NC, class Ptr>
-__device__ double multisect(Ptr d, Ptr e2, int n, int k, int g, int G, double glo, double ghi,
-                            double pivmin)
-{
-    double lo = glo, hi = ghi;
-    for (int it = 0; it < 64; ++it) {
-        if (!(hi - lo > 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin)) break;
-        const double h = (hi - lo) / (double)(NC * G + 1);
-        double x[NC], q[NC];
-        int c[NC];
-        // a pivot below pivmin in magnitude becomes -pivmin, so it is
-        // negative after that exactly when it was below pivmin: the count
-        // takes that test, beside the clamp rather than after it
-        auto step = [&](double di, double ei) {
-#pragma unroll
-            for (int u = 0; u < NC; ++u) {
-                q[u] = di - x[u] - ei * recip_nr(q[u]);
-                c[u] += q[u] < pivmin;
-                if (fabs(q[u]) < pivmin) q[u] = -pivmin;
-            }
-        };
-#pragma unroll
-        for (int u = 0; u < NC; ++u) {
-            x[u] = lo + h * (double)(NC * g + u + 1);
-            q[u] = d[0] - x[u];
-            c[u] = q[u] < pivmin;
-            if (fabs(q[u]) < pivmin) q[u] = -pivmin;
-        }
-        // the next step's coefficients are read a step ahead, so the LDS
-        // latency overlaps the current step's arithmetic (the last step
-        // peeled: no test inside the loop)
-        if (n > 1) {
-            double dn = d[1], en = e2[0];
-            for (int i = 1; i + 1 < n; ++i) {
-                const double di = dn, ei = en;
-                dn = d[i + 1];
-                en = e2[i];
-                step(di, ei);
-            }
-            step(dn, en);
-        }
-        double nlo = lo, nhi = hi;
-#pragma unroll
-        for (int u = 0; u < NC; ++u) {
-            if (c[u] <= k) nlo = fmax(nlo, x[u]);
-            else nhi = fmin(nhi, x[u]);
-        }
-        for (int off = 1; off < G; off <<= 1) {
-            nlo = fmax(nlo, __shfl_xor(nlo, off));
-            nhi = fmin(nhi, __shfl_xor(nhi, off));
-        }
-        if (nlo == lo && nhi == hi) break;  // no representable progress
-        lo = nlo;
-        hi = nhi;
-    }
-    return 0.5 * (lo + hi);
-}
-
-__global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks)
+__global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks, int eig_max)
 {
     __shared__ double v[SVD_SMALL_K];
     __shared__ double2 uw[SVD_SMALL_K];
@@ -648,7 +550,7 @@ __global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks)
     __shared__ double wp[EIG_THREADS];
     const SvdTask& t = tasks[blockIdx.x];
     const int n = (int)t.K;
-    if (n > SVD_SMALL_K) return;  // (uniform) a larger matrix takes the many-workgroup path
+    if (n > eig_max) return;  // (uniform) a larger matrix takes a group of workgroups
     const int tid = threadIdx.x;
     if (n <= EIG_LDS_K) {
         for (int q = tid; q < n * n; q += EIG_THREADS) As[q] = t.gram[q];
@@ -660,70 +562,19 @@ __global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks)
         typedef __attribute__((address_space(1))) double gdouble;
         tridiagonalize((gdouble*)t.gram, n, v, uw, wp, d, e2, red);
     }
-    // the tridiagonal form and its bounds for k_svd_count
     for (int i = tid; i < n; i += EIG_THREADS) {
         t.tri[i] = d[i];
         t.tri[n + i] = e2[i];
     }
-    if (tid == 0) {
-        double glo, ghi, pivmin;
-        gershgorin((const lds_f64*)d, (const lds_f64*)e2, n, glo, ghi, pivmin);
-        t.tri[2 * n] = glo;
-        t.tri[2 * n + 1] = ghi;
-        t.tri[2 * n + 2] = pivmin;
-    }
-}
-
-// every eigenvalue of the tridiagonal forms k_svd_eig wrote: one wave per
-// EIG_PER_ITEM eigenvalues of a task (work items numbered from the task's
-// eig0), COUNT_G threads per eigenvalue with COUNT_C chains each.  The
-// counts are bound by instruction issue over the device as a whole (the
-// work is rounds x points per round, and fewer points per round cost fewer
-// instructions than the extra rounds add) and by each chain's latency within
-// a wave; four threads of one chain (four points a round, 22 rounds for 52
-// bits) spread a 128-side matrix over eight waves, about one wave per SIMD
-// over the whole device for 64 attention-shaped tensors.  Measured on those:
-// 0.15 ms; 2, 8 or 16 threads of one chain 0.21, 0.16, 0.22 ms; four threads
-// of two chains 0.19 ms, of four 0.27 ms
-constexpr int COUNT_G = 4;
-constexpr int COUNT_C = 1;
-static_assert(EIG_PER_ITEM * COUNT_G == GW, "one wave per work item");
-
-__global__ __launch_bounds__(GW) void k_svd_count(const SvdTask* tasks, int n_tasks,
-                                                 int64_t n_items)
-{
-    __shared__ double ds[SVD_SMALL_K], es[SVD_SMALL_K];
-    const int64_t item = blockIdx.x;
-    if (item >= n_items) return;  // uniform
-    int lo = 0, hi = n_tasks - 1;  // the last task whose first item is <= item
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tasks[mid].eig0 <= item) lo = mid; else hi = mid - 1;
-    }
-    const SvdTask& t = tasks[lo];
-    const int n = (int)t.K;
-    const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += GW) {
-        ds[i] = t.tri[i];
-        es[i] = t.tri[n + i];
-    }
-    const double glo = t.tri[2 * n], ghi = t.tri[2 * n + 1], pivmin = t.tri[2 * n + 2];
-    __syncthreads();
-    // (whole groups of COUNT_G lanes share k and leave together)
-    const int k = (int)(item - t.eig0) * EIG_PER_ITEM + tid / COUNT_G, g = tid % COUNT_G;
-    if (k >= n) return;
-    const double lam = multisect<COUNT_C>((const lds_f64*)ds, (const lds_f64*)es, n, k, g,
-                                          COUNT_G, glo, ghi, pivmin);
-    if (g == 0) t.out[n - 1 - k] = sqrt(fmax(lam, 0.0));
 }
 
 // ---------------------------------------------------------------------------
-// Gram matrices larger than SVD_SMALL_K: one Householder step is four
+// Gram matrices larger than SVD_GROUP_MAX: one Householder step is four
 // launches over the whole device (the reflector; the product p = beta A u in
 // 64-column x 256-row blocks; the blocks' partial sums added in block order,
-// with K = beta (p . u) / 2; the rank-two update in the same blocks), then the
-// tridiagonal matrix's eigenvalues by multisection with enough threads per
-// eigenvalue to fill the device.  The matrix stays in place in the workspace.
+// with K = beta (p . u) / 2; the rank-two update in the same blocks), until
+// what is left fits a group of workgroups.  The matrix stays in place in the
+// workspace.
 // ---------------------------------------------------------------------------
 constexpr int HH_THREADS = 1024;  // one-workgroup kernels
 constexpr int HH_COLS = 64;       // columns per block (one per lane)
@@ -731,7 +582,6 @@ constexpr int HH_ROWS = 256;      // rows per block (64 per wave)
 
 struct HhState {
     double beta, K2;
-    double glo, ghi, pivmin;
     int32_t skip;  // the step's column is already reduced
 };
 
@@ -849,70 +699,14 @@ __global__ __launch_bounds__(256) void k_hh_update(double* A, int n, int k, cons
     }
 }
 
-// the last 2 x 2 corner; then the Gershgorin interval (one workgroup)
-__global__ __launch_bounds__(HH_THREADS) void k_hh_finish(const double* A, int n, double* d,
-                                                          double* e2, HhState* hs)
+// the last 2 x 2 corner
+__global__ void k_hh_finish(const double* A, int n, double* d, double* e2)
 {
-    __shared__ double red[3][HH_THREADS / 64];
-    __shared__ double de[2][3];
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        // d[n-2], e2[n-2], d[n-1] (n > SVD_SMALL_K >= 2)
-        de[0][0] = A[(size_t)(n - 2) * n + (n - 2)];
-        const double en = A[(size_t)(n - 1) * n + (n - 2)];
-        de[0][1] = en * en;
-        de[0][2] = A[(size_t)(n - 1) * n + (n - 1)];
-        d[n - 2] = de[0][0];
-        e2[n - 2] = de[0][1];
-        d[n - 1] = de[0][2];
-    }
-    __syncthreads();
-    // per-thread ranges of the Gershgorin bounds, then one reduction
-    double glo = INFINITY, ghi = -INFINITY, emax = 0.0;
-    for (int i = tid; i < n; i += HH_THREADS) {
-        const double di = (i == n - 2) ? de[0][0] : (i == n - 1) ? de[0][2] : d[i];
-        const double el = (i > 0) ? ((i - 1 == n - 2) ? de[0][1] : e2[i - 1]) : 0.0;
-        const double er = (i + 1 < n) ? ((i == n - 2) ? de[0][1] : e2[i]) : 0.0;
-        const double r = sqrt(el) + sqrt(er);
-        glo = fmin(glo, di - r);
-        ghi = fmax(ghi, di + r);
-        if (i + 1 < n) emax = fmax(emax, er);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        glo = fmin(glo, __shfl_xor(glo, off));
-        ghi = fmax(ghi, __shfl_xor(ghi, off));
-        emax = fmax(emax, __shfl_xor(emax, off));
-    }
-    if ((tid & 63) == 0) {
-        red[0][tid >> 6] = glo;
-        red[1][tid >> 6] = ghi;
-        red[2][tid >> 6] = emax;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int u = 1; u < HH_THREADS / 64; ++u) {
-            glo = fmin(glo, red[0][u]);
-            ghi = fmax(ghi, red[1][u]);
-            emax = fmax(emax, red[2][u]);
-        }
-        const double span = fmax(fabs(glo), fabs(ghi));
-        const double pivmin = 0x1p-1000 * fmax(1.0, emax);
-        hs->glo = glo - (2.0 * DBL_EPSILON * span + pivmin);
-        hs->ghi = ghi + (2.0 * DBL_EPSILON * span + pivmin);
-        hs->pivmin = pivmin;
-    }
-}
-
-// every eigenvalue, G threads each (the grid holds exactly n G threads,
-// rounded up to whole workgroups; whole groups leave together)
-__global__ __launch_bounds__(256) void k_hh_bisect(const double* d, const double* e2, int n, int G,
-                                                   const HhState* hs, double* out)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = (int)(t / G), g = (int)(t % G);
-    if (k >= n) return;
-    const double lam = multisect<4>(d, e2, n, k, g, G, hs->glo, hs->ghi, hs->pivmin);
-    if (g == 0) out[n - 1 - k] = sqrt(fmax(lam, 0.0));
+    if (threadIdx.x != 0) return;
+    d[n - 2] = A[(size_t)(n - 2) * n + (n - 2)];
+    const double en = A[(size_t)(n - 1) * n + (n - 2)];
+    e2[n - 2] = en * en;
+    d[n - 1] = A[(size_t)(n - 1) * n + (n - 1)];
 }
 
 __global__ __launch_bounds__(64) void k_svd_match(const SpecDesc* da, int na, const double* sa,
@@ -986,13 +780,13 @@ __global__ __launch_bounds__(64) void k_svd_match(const SpecDesc* da, int na, co
 }  // namespace
 
 hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n_items_narrow,
-                      int n_whole, int64_t n_items_whole, int64_t n_items, int64_t n_eig_items,
-                      double* gram, int64_t gram_len, hipStream_t stream)
+                      int n_whole, int64_t n_items_whole, int64_t n_items, int eig_max,
+                      double* gram, int64_t clear_len, hipStream_t stream)
 {
     if (n_tasks <= 0) return hipSuccess;
-    const int64_t cb = min((gram_len + 255) / 256, (int64_t)4096);
+    const int64_t cb = min((clear_len + 255) / 256, (int64_t)4096);
     hipLaunchKernelGGL(k_svd_clear, dim3((unsigned)max(cb, (int64_t)1)), dim3(256), 0, stream,
-                       gram, gram_len);
+                       gram, clear_len);
     // tasks [0, n_narrow): K <= GRAM_NARROW, one 32-side block; then n_whole
     // with K in (64, GRAM_WHOLE], the whole upper triangle per workgroup; the
     // rest in 64-side blocks
@@ -1007,31 +801,29 @@ hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n
     if (n_items > 0 && n_blocked > 0)
         hipLaunchKernelGGL(k_gram<64>, dim3((unsigned)n_items), dim3(64 * 64 / 4), 0, stream,
                            tasks + n_narrow + n_whole, n_blocked, n_items);
-    hipLaunchKernelGGL(k_svd_eig, dim3((unsigned)n_tasks), dim3(EIG_THREADS), 0, stream, tasks);
-    if (n_eig_items > 0)
-        hipLaunchKernelGGL(k_svd_count, dim3((unsigned)n_eig_items), dim3(GW), 0, stream, tasks,
-                           n_tasks, n_eig_items);
+    if (eig_max > 0)
+        hipLaunchKernelGGL(k_svd_eig, dim3((unsigned)n_tasks), dim3(EIG_THREADS), 0, stream, tasks,
+                           eig_max);
     return hipGetLastError();
 }
 
 int64_t svd_large_scratch(int n)
 {
     const int64_t R = (n + HH_ROWS - 1) / HH_ROWS;
-    // u, p, d, e2, the row blocks' partial sums, the step state
-    return 4 * (int64_t)n + R * n + (int64_t)((sizeof(HhState) + 7) / 8);
+    // u, p, the row blocks' partial sums, the step state
+    return 2 * (int64_t)n + R * n + (int64_t)((sizeof(HhState) + 7) / 8);
 }
 
-hipError_t launch_svd_large(double* A, int n, double* scratch, double* out, hipStream_t stream)
+hipError_t launch_svd_large(double* A, int n, int stop, double* scratch, double* d, double* e2,
+                            hipStream_t stream)
 {
-    if (n <= SVD_SMALL_K) return hipErrorInvalidValue;
+    if (n < 3 || stop < 0 || stop > n - 2) return hipErrorInvalidValue;
     const int R = (n + HH_ROWS - 1) / HH_ROWS;
     double* u = scratch;
     double* p = u + n;
-    double* d = p + n;
-    double* e2 = d + n;
-    double* part = e2 + n;
+    double* part = p + n;
     HhState* hs = reinterpret_cast<HhState*>(part + (size_t)R * n);
-    for (int k = 0; k + 2 < n; ++k) {
+    for (int k = 0; k < stop; ++k) {
         const int m = n - k - 1;
         const dim3 blocks((unsigned)((m + HH_COLS - 1) / HH_COLS), (unsigned)((m + HH_ROWS - 1) / HH_ROWS));
         hipLaunchKernelGGL(k_hh_reflector, dim3(1), dim3(HH_THREADS), 0, stream, A, n, k, u, d, e2,
@@ -1041,13 +833,8 @@ hipError_t launch_svd_large(double* A, int n, double* scratch, double* out, hipS
                            (int)blocks.y, p, hs);
         hipLaunchKernelGGL(k_hh_update, blocks, dim3(256), 0, stream, A, n, k, u, p, hs);
     }
-    hipLaunchKernelGGL(k_hh_finish, dim3(1), dim3(HH_THREADS), 0, stream, A, n, d, e2, hs);
-    // threads per eigenvalue: enough for about 32K threads in all
-    int G = 1;
-    while (G < 8 && (int64_t)G * n < 32768) G *= 2;
-    const int64_t threads = (int64_t)n * G;
-    hipLaunchKernelGGL(k_hh_bisect, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream,
-                       d, e2, n, G, hs, out);
+    if (stop == n - 2)
+        hipLaunchKernelGGL(k_hh_finish, dim3(1), dim3(64), 0, stream, A, n, d, e2);
     return hipGetLastError();
 }
 

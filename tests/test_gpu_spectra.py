@@ -191,3 +191,60 @@ def test_large_rank_deficient_unfolding():
     log("[spectra] rank-deficient 700 x 800")
     _, _, (got,) = _gpu_lists([T])
     _assert_spectra(got, S.invariants(T), "rank-deficient 700 x 800")
+
+
+# Sides of the group reduction's classes and their edges: the smallest, sides
+# whose rows per member change to fit the slots (489, 505, 1017), whole
+# classes, and one past each (reduced in two classes, one taking over from the
+# other); 3073 and above keep some rows in LDS and in memory
+@pytest.mark.parametrize("K", [129, 130, 257, 489, 505, 512, 513, 1017, 1024, 1025, 2048, 2049])
+def test_group_reduced_sides(K):
+    rng = np.random.default_rng(K)
+    T = rng.standard_normal((K, K + 37)).astype(np.float32)
+    T[:, :5] *= 30.0
+    T[3] *= 1e-3
+    log(f"[spectra] group-reduced side {K}")
+    _, _, (got,) = _gpu_lists([T])
+    _assert_spectra(got, S.invariants(T), f"side {K}")
+
+
+# the largest class, and a side beyond it (device-wide steps down to 4096, then
+# the group): eigenvalues of the fp64 Gram matrix, within a few thousand
+# rounding units of the largest (a sum of 4,200 products, then the reduction)
+@pytest.mark.parametrize("K", [3072, 3073, 4096, 4099])
+def test_group_reduced_large_sides(K):
+    rng = np.random.default_rng(K)
+    T = rng.standard_normal((K, K + 100)).astype(np.float32)
+    log(f"[spectra] group-reduced side {K}")
+    _, _, (got,) = _gpu_lists([T])
+    X = T.astype(np.float64)
+    want = np.linalg.eigvalsh(X @ X.T)[::-1]
+    lam = np.asarray(got[0]) ** 2
+    assert np.max(np.abs(lam - want)) <= 1e-12 * want[0]
+
+
+def test_group_reduction_batch():
+    """More groups than fit at once, of several classes, beside sides that one
+    workgroup reduces: launch rounds and the hand-over between classes."""
+    rng = np.random.default_rng(31)
+    shapes = [(300, 310)] * 9 + [(700, 720), (130, 140), (520, 530), (60, 400), (1100, 1120),
+                                 (512, 700), (2, 200, 3, 150)]
+    Ts = [rng.standard_normal(sh).astype(np.float32) for sh in shapes]
+    log(f"[spectra] group batch {shapes}")
+    _, _, got = _gpu_lists(Ts)
+    for T, g, sh in zip(Ts, got, shapes):
+        _assert_spectra(g, S.invariants(T), f"group batch {sh}")
+
+
+def test_zero_and_diagonal_tensors():
+    """Splitting tridiagonal forms: all zeros, a diagonal matrix, and repeated
+    diagonal entries (every off-diagonal entry zero)."""
+    Z = np.zeros((200, 210), np.float32)
+    D = np.zeros((150, 160), np.float32)
+    D[np.arange(150), np.arange(150)] = np.linspace(1.0, 2.0, 150).astype(np.float32)
+    R = np.zeros((40, 50), np.float32)
+    R[np.arange(40), np.arange(40)] = np.repeat(np.float32([1.0, 0.0, 3.0, 1e-3]), 10)
+    _, _, (z, d, r) = _gpu_lists([Z, D, R])
+    assert np.all(np.asarray(z[0]) == 0.0)
+    _assert_spectra(d, S.invariants(D), "diagonal")
+    _assert_spectra(r, S.invariants(R), "repeated diagonal")
