@@ -1905,12 +1905,13 @@ struct InvPlan {
     std::vector<int64_t> spec_off;
     int n_narrow = 0, n_whole = 0;
     int64_t gram_len = 0, n_items = 0, n_items_narrow = 0, n_items_whole = 0;
-    // eigenvalue work items (in task order, 64 / eig_lanes values each), the
+    // eigenvalue work items (in task order, STURM_LANES / eig_lanes values each), the
     // doubles of the tridiagonal forms, and the exchange words of the sides that
     // a group of workgroups may reduce
     int64_t n_eig_items = 0, tri_len = 0, n_words = 0;
     int eig_lanes = 1;
-    int large_k = 0;  // largest Gram side above mag::SVD_SMALL_K (0: none)
+    int max_k = 0;    // largest Gram side
+    int large_k = 0;  // the same above mag::SVD_SMALL_K (0: none)
 };
 
 // the part of a Gram side that a group of workgroups reduces (a larger one is
@@ -1935,6 +1936,7 @@ int plan_invariants(const mag_tensor* ts, int32_t n, InvPlan& pl)
             unfolding_task(&ts[i], g, task);
             const int64_t items = (int64_t)task.nt * (task.nt + 1) / 2 * task.nchunk;
             pl.gram_len += task.K * task.K;
+            pl.max_k = std::max(pl.max_k, (int)task.K);
             if (task.K > mag::SVD_SMALL_K) pl.large_k = std::max(pl.large_k, (int)task.K);
             if (task.K <= mag::GRAM_NARROW) {
                 task.item0 = pl.n_items_narrow;
@@ -1962,7 +1964,7 @@ int plan_invariants(const mag_tensor* ts, int32_t n, InvPlan& pl)
     pl.tasks.insert(pl.tasks.end(), wide.begin(), wide.end());
     pl.spec_off.insert(pl.spec_off.end(), wide_off.begin(), wide_off.end());
     pl.eig_lanes = mag::sturm_lanes(so);
-    const int per = 64 / pl.eig_lanes;
+    const int per = mag::STURM_LANES / pl.eig_lanes;
     for (auto& t : pl.tasks) {
         t.eig0 = pl.n_eig_items;
         pl.n_eig_items += (t.K + per - 1) / per;
@@ -1996,29 +1998,24 @@ size_t carve_invariants(const InvPlan& pl, void* ws, InvWorkspace& w)
     return c.off;
 }
 
-// the largest Gram side that one workgroup reduces in this call (the larger
-// ones take groups of workgroups).  Sides up to 128 are reduced in LDS; above,
-// one workgroup per matrix works from L2, about 4 + 39 (K / 512)^2 us a step
-// (measured: 21.9 ms at K = 512), up to one matrix per CU at a time; a group
-// takes about 3.3 us a step whatever the side (1.67 ms at K = 512), but only as
-// many matrices at a time as have room (launch rounds)
-int eig_side(const InvPlan& pl)
+// whether the Gram sides in (TRI_MIDDLE, SVD_SMALL_K] are reduced by one
+// workgroup each in this call, rather than by groups of workgroups.  One
+// workgroup works from L2, about 4 + 39 (K / 512)^2 us a step (measured: 21.9
+// ms at K = 512), up to one matrix per CU at a time; a group takes about 3.3 us
+// a step whatever the side (1.67 ms at K = 512), but only as many matrices at a
+// time as have room (launch rounds)
+bool one_workgroup_each(const InvPlan& pl)
 {
     std::vector<int> mid;  // in the order in which the groups would be launched
-    int kmax = 0;
     for (const auto& t : pl.tasks)
-        if (t.K >= mag::SVD_GROUP_MIN && t.K <= mag::SVD_SMALL_K) {
-            mid.push_back((int)t.K);
-            kmax = std::max(kmax, (int)t.K);
-        }
-    if (mid.empty()) return mag::SVD_SMALL_K;
+        if (t.K >= mag::SVD_GROUP_MIN && t.K <= mag::SVD_SMALL_K) mid.push_back((int)t.K);
+    if (mid.empty()) return false;
     for (int k : mid)
-        if (!mag::tri_group_fits(k)) return mag::SVD_SMALL_K;
+        if (!mag::tri_group_fits(k)) return true;
     std::sort(mid.begin(), mid.end(), [](int a, int b) { return a > b; });
-    const double r = (double)kmax / 512.0;
+    const double r = (double)mid[0] / 512.0;
     const double one = (4.0 + 39.0 * r * r) * (double)((mid.size() + 255) / 256);
-    const double group = 3.3 * (double)mag::tri_group_rounds(mid.data(), (int)mid.size());
-    return group < one ? mag::SVD_GROUP_MIN - 1 : mag::SVD_SMALL_K;
+    return !(3.3 * (double)mag::tri_group_rounds(mid.data(), (int)mid.size()) < one);
 }
 
 // spectra descriptors of a tensor set: offsets in the order mag_invariants writes
@@ -2087,8 +2084,8 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
     if (workspace_bytes < need) return fail(MAG_E_WORKSPACE, "workspace too small");
     carve_invariants(pl, workspace, w);
     int64_t go = 0, to = 0, wo = 0;
-    const int eig_max = eig_side(pl);
-    bool any_eig = false;
+    const bool one_each = one_workgroup_each(pl);
+    bool small = false, middle = false;
     std::vector<mag::TriMatrix> groups;
     for (size_t i = 0; i < pl.tasks.size(); ++i) {
         mag::SvdTask& t = pl.tasks[i];
@@ -2098,10 +2095,11 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
         go += t.K * t.K;
         t.tri = w.tri + to;
         to += mag::tri_len(K);
-        any_eig = any_eig || K <= eig_max;
+        small = small || K <= mag::TRI_SMALL;
+        middle = middle || (K > mag::TRI_SMALL && K <= mag::TRI_MIDDLE);
         if (K < mag::SVD_GROUP_MIN) continue;
         const int side = group_side(K), k0 = K - side;
-        if (K > eig_max && mag::tri_group_fits(side))
+        if (!(one_each && K <= mag::SVD_SMALL_K) && mag::tri_group_fits(side))
             groups.push_back(mag::TriMatrix{t.gram + (size_t)k0 * K + k0, t.tri + k0,
                                             t.tri + K + k0, w.words + wo, K, side, 0u});
         wo += mag::tri_group_words(side);
@@ -2114,13 +2112,15 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
                             hipMemcpyHostToDevice, stream)) != hipSuccess)
         return hip_fail(e, "task copy");
     if ((e = mag::launch_svd(w.tasks, (int)pl.tasks.size(), pl.n_narrow, pl.n_items_narrow,
-                             pl.n_whole, pl.n_items_whole, pl.n_items, any_eig ? eig_max : 0,
-                             w.gram, w.clear_len, stream)) != hipSuccess)
+                             pl.n_whole, pl.n_items_whole, pl.n_items, one_each, w.gram,
+                             w.clear_len, stream)) != hipSuccess)
         return hip_fail(e, "invariant kernels");
+    if ((e = mag::launch_tri_one(w.tasks, (int)pl.tasks.size(), small, middle, stream)) != hipSuccess)
+        return hip_fail(e, "reduction kernels");
     // sides beyond the groups' reach: device-wide steps down to it (or, on a
     // device with too few CUs for the group, all the way)
     for (const auto& t : pl.tasks) {
-        if (t.K <= eig_max) continue;
+        if (t.K <= mag::SVD_SMALL_K) continue;
         const int K = (int)t.K, side = group_side(K);
         const int stop = mag::tri_group_fits(side) ? K - side : K - 2;
         if (stop > 0 && (e = mag::launch_svd_large(t.gram, K, stop, w.large, t.tri, t.tri + K,
@@ -2137,7 +2137,7 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
             return hip_fail(e, "status copy");
     }
     if ((e = mag::launch_sturm(w.tasks, (int)pl.tasks.size(), pl.n_eig_items, pl.eig_lanes,
-                               stream)) != hipSuccess)
+                               pl.max_k, stream)) != hipSuccess)
         return hip_fail(e, "eigenvalue kernels");
     // (the task table on the host stays alive until the copy is done)
     if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "synchronize");

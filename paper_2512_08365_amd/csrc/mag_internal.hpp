@@ -266,12 +266,12 @@ hipError_t launch_aggregate(const GroupParams& p, hipStream_t stream);
 // multi-mode SVD invariants (Section 4.2): one task per (tensor, unfolding)
 constexpr int SVD_MAX_RANK = 5;
 constexpr int SVD_MAX_K = 8192;       // largest Gram side (min(M, N) of an unfolding)
-constexpr int SVD_SMALL_K = 512;      // Gram sides reduced by one workgroup (larger: many)
+constexpr int SVD_SMALL_K = 512;      // largest Gram side one workgroup can reduce
 constexpr int SVD_MAX_UNF = 15;       // unfoldings of a rank-5 tensor, complements folded
 constexpr int64_t GRAM_CHUNK = 2048;  // unfolding columns per Gram work item
 constexpr int64_t GRAM_CHUNK_NARROW = 1024;  // the same for K <= GRAM_NARROW (one 32-side block)
 constexpr int GRAM_NARROW = 32;       // Gram sides up to this use 32-side blocks (else 64)
-constexpr int SVD_GROUP_MIN = 129;    // Gram sides that a group of workgroups can reduce
+constexpr int SVD_GROUP_MIN = 193;    // Gram sides that a group of workgroups can reduce
 constexpr int SVD_GROUP_MAX = 4096;
 constexpr int GRAM_WHOLE = 128;       // sides in (64, GRAM_WHOLE]: the whole triangle per item
 constexpr int64_t GRAM_CHUNK_WHOLE = 1024;  // unfolding columns per item for those sides
@@ -286,7 +286,7 @@ struct SvdTask {
     double* out;     // [K] singular values, descending
     int64_t item0;   // first Gram work item of this task (within its block size's launch)
     double* tri;     // the tridiagonal form: d[K], e2[K], then as the counts read it (tri_len)
-    int64_t eig0;    // first eigenvalue work item (one wave's eigenvalues each)
+    int64_t eig0;    // first eigenvalue work item (one workgroup's eigenvalues each)
     int32_t nt;      // row blocks: 1 when K <= GRAM_NARROW or 64 < K <= GRAM_WHOLE, else ceil(K / 64)
     int32_t nchunk;  // column chunks of L: GRAM_CHUNK_NARROW, GRAM_CHUNK_WHOLE or GRAM_CHUNK columns
 };
@@ -299,9 +299,9 @@ struct SpecDesc {
     int64_t len[SVD_MAX_UNF];
 };
 
-// a tridiagonal form's place: d, squared off-diagonals, then tri_padded(K) + 8
-// pairs {d_i, e2_{i-1}} scaled for the counts (the last 8 only read ahead),
-// the scaled bounds of the eigenvalues and the scale
+// a tridiagonal form's place: d, squared off-diagonals, then tri_padded(K)
+// pairs {d_i, e2_{i-1}} scaled for the counts, the scaled bounds of the
+// eigenvalues and the scale
 __host__ __device__ inline int tri_padded(int n) { return (n + 7) / 8 * 8; }
 __host__ __device__ inline double2* tri_pairs(double* tri, int n)
 {
@@ -309,17 +309,18 @@ __host__ __device__ inline double2* tri_pairs(double* tri, int n)
 }
 __host__ __device__ inline double* tri_bounds(double* tri, int n)
 {
-    return tri + 4 * tri_padded(n) + 16;
+    return tri + 4 * tri_padded(n);
 }
-__host__ __device__ inline int64_t tri_len(int n) { return 4 * (int64_t)tri_padded(n) + 24; }
+__host__ __device__ inline int64_t tri_len(int n) { return 4 * (int64_t)tri_padded(n) + 8; }
 
 // Gram matrices and exchange words (clear_len doubles, zeroed; the matrices
-// then accumulated), and the tridiagonal forms of the tasks with K <= eig_max;
+// then accumulated), and, with one_each, the tridiagonal forms of the tasks
+// with TRI_MIDDLE < K <= SVD_SMALL_K, one workgroup each;
 // the first n_narrow tasks (K <= GRAM_NARROW) are numbered by their own
 // n_items_narrow work items, the next n_whole (64 < K <= GRAM_WHOLE) by
 // n_items_whole, the others by n_items
 hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n_items_narrow,
-                      int n_whole, int64_t n_items_whole, int64_t n_items, int eig_max,
+                      int n_whole, int64_t n_items_whole, int64_t n_items, bool one_each,
                       double* gram, int64_t clear_len, hipStream_t stream);
 
 // one symmetric matrix (both triangles, row stride lda, overwritten) and where
@@ -353,6 +354,12 @@ struct TriGroupJobs {
     int32_t count;
     TriGroupJob job[TRI_GROUP_JOBS];
 };
+// tridiagonal forms of the tasks with sides up to TRI_SMALL (`small`) and from
+// there up to TRI_MIDDLE (`middle`), one workgroup each, in registers
+constexpr int TRI_SMALL = 128;
+constexpr int TRI_MIDDLE = 192;
+hipError_t launch_tri_one(const SvdTask* tasks, int n_tasks, bool small, bool middle,
+                          hipStream_t stream);
 // whether a group of workgroups can reduce side n on this device; the launches
 // that a batch takes (matrices of one class side by side while they fit)
 bool tri_group_fits(int n);
@@ -366,10 +373,12 @@ hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream
 int64_t svd_large_scratch(int n);
 hipError_t launch_svd_large(double* gram, int n, int stop, double* scratch, double* d, double* e2,
                             hipStream_t stream);
-// every eigenvalue of the tasks' tridiagonal forms: G lanes each, n_items
-// waves of 64 / G eigenvalues; sigma = sqrt(max(lambda, 0)), descending
+// every eigenvalue of the tasks' tridiagonal forms (sides up to n_max): G lanes
+// each, n_items workgroups of STURM_LANES / G eigenvalues; sigma =
+// sqrt(max(lambda, 0)), descending
+constexpr int STURM_LANES = 256;
 int sturm_lanes(int64_t values);
-hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G,
+hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G, int n_max,
                         hipStream_t stream);
 // match[i * nb + j] = 1 when tensor i of A and tensor j of B have matching invariants
 hipError_t launch_svd_match(const SpecDesc* da, int na, const double* sa, const SpecDesc* db,

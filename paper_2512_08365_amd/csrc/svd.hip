@@ -14,10 +14,10 @@
 //   mirror) with fp64 atomics.  The elements of X are gathered through the
 //   unfolding's mixed-radix offsets.  Sides up to 32: one 32-side block;
 //   sides in (64, 128]: k_gram_whole, the whole triangle per workgroup.
-// k_svd_eig: one workgroup per task: Householder reduction of the Gram
-//   matrix (in LDS up to side 128, else in place in global memory) to
-//   tridiagonal form; larger matrices take groups of workgroups, and every
-//   form's eigenvalues come from Sturm counts (tridiag.hip).
+// k_svd_eig: Gram sides in (TRI_MIDDLE, SVD_SMALL_K] of a batch that holds many:
+//   one workgroup per task, Householder reduction to tridiagonal form in place
+//   in global memory; the other sides' reductions, and every form's
+//   eigenvalues, are in tridiag.hip.
 // k_svd_match: one workgroup per tensor pair: which spectra of the two lists
 //   are close, then a one-to-one pairing by augmenting paths.
 
@@ -425,12 +425,8 @@ __device__ double block_sum(double v, double (*red)[EIG_THREADS / 64], int& flip
     return s;
 }
 
-constexpr int EIG_LDS_K = 128;  // Gram matrices up to this side are reduced in LDS
-
 // Householder reduction of the symmetric n x n matrix A (row stride n) to
 // tridiagonal form: d[k] the diagonal, e2[k] the squared off-diagonal
-typedef __attribute__((address_space(3))) double lds_f64;
-
 template <class Ptr>
 __device__ void tridiagonalize(Ptr A, int n, double* v, double2* uw, double* wp, double* d,
                                double* e2, double (*red)[EIG_THREADS / 64])
@@ -446,10 +442,9 @@ __device__ void tridiagonalize(Ptr A, int n, double* v, double2* uw, double* wp,
     for (int k = 0; k + 2 < n; ++k) {
         const int m = n - k - 1;
         double tail = 0.0;
-        // column k below the diagonal, read as row k right of it (contiguous:
-        // no bank conflicts in LDS, coalesced in global memory); the two agree
-        // up to the rounding of the updates, which keep the matrix symmetric
-        // in exact arithmetic
+        // column k below the diagonal, read as row k right of it (contiguous); the
+        // two agree up to the rounding of the updates, which keep the matrix
+        // symmetric in exact arithmetic
         for (int i = tid; i < m; i += EIG_THREADS) {
             const double x = A[(size_t)k * n + (k + 1 + i)];
             v[i] = x;
@@ -540,29 +535,21 @@ __device__ void tridiagonalize(Ptr A, int n, double* v, double2* uw, double* wp,
     __syncthreads();
 }
 
-__global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks, int eig_max)
+__global__ __launch_bounds__(EIG_THREADS) void k_svd_eig(const SvdTask* tasks)
 {
     __shared__ double v[SVD_SMALL_K];
     __shared__ double2 uw[SVD_SMALL_K];
     __shared__ double d[SVD_SMALL_K], e2[SVD_SMALL_K];
     __shared__ double red[2][EIG_THREADS / 64];
-    __shared__ double As[EIG_LDS_K * EIG_LDS_K];
     __shared__ double wp[EIG_THREADS];
     const SvdTask& t = tasks[blockIdx.x];
     const int n = (int)t.K;
-    if (n > eig_max) return;  // (uniform) a larger matrix takes a group of workgroups
-    const int tid = threadIdx.x;
-    if (n <= EIG_LDS_K) {
-        for (int q = tid; q < n * n; q += EIG_THREADS) As[q] = t.gram[q];
-        __syncthreads();
-        tridiagonalize((lds_f64*)As, n, v, uw, wp, d, e2, red);  // ds_ instructions
-    } else {
-        // global-memory instructions (generic ones would also count against
-        // the LDS waits)
-        typedef __attribute__((address_space(1))) double gdouble;
-        tridiagonalize((gdouble*)t.gram, n, v, uw, wp, d, e2, red);
-    }
-    for (int i = tid; i < n; i += EIG_THREADS) {
+    if (n <= TRI_MIDDLE || n > SVD_SMALL_K) return;  // (uniform) reduced elsewhere
+    // global-memory instructions (generic ones would also count against the
+    // LDS waits)
+    typedef __attribute__((address_space(1))) double gdouble;
+    tridiagonalize((gdouble*)t.gram, n, v, uw, wp, d, e2, red);
+    for (int i = threadIdx.x; i < n; i += EIG_THREADS) {
         t.tri[i] = d[i];
         t.tri[n + i] = e2[i];
     }
@@ -780,7 +767,7 @@ __global__ __launch_bounds__(64) void k_svd_match(const SpecDesc* da, int na, co
 }  // namespace
 
 hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n_items_narrow,
-                      int n_whole, int64_t n_items_whole, int64_t n_items, int eig_max,
+                      int n_whole, int64_t n_items_whole, int64_t n_items, bool one_each,
                       double* gram, int64_t clear_len, hipStream_t stream)
 {
     if (n_tasks <= 0) return hipSuccess;
@@ -801,9 +788,8 @@ hipError_t launch_svd(const SvdTask* tasks, int n_tasks, int n_narrow, int64_t n
     if (n_items > 0 && n_blocked > 0)
         hipLaunchKernelGGL(k_gram<64>, dim3((unsigned)n_items), dim3(64 * 64 / 4), 0, stream,
                            tasks + n_narrow + n_whole, n_blocked, n_items);
-    if (eig_max > 0)
-        hipLaunchKernelGGL(k_svd_eig, dim3((unsigned)n_tasks), dim3(EIG_THREADS), 0, stream, tasks,
-                           eig_max);
+    if (one_each)
+        hipLaunchKernelGGL(k_svd_eig, dim3((unsigned)n_tasks), dim3(EIG_THREADS), 0, stream, tasks);
     return hipGetLastError();
 }
 

@@ -180,11 +180,10 @@ __device__ __forceinline__ bool poll_words(const uint64_t* w, int stride, uint32
 }
 
 // square root and reciprocal within an ulp or two (estimates refined by
-// Newton steps: half the latency of the correctly rounded ones); arguments
-// whose estimate could leave the range take the library's
+// Newton steps: half the latency of the correctly rounded ones), for arguments
+// from 2^-900 to 2^900
 __device__ __forceinline__ double sqrt_near(double v)
 {
-    if (!(v >= 0x1p-900 && v <= 0x1p900)) return sqrt(v);  // uniform
     const double y = __builtin_amdgcn_rsq(v);
     double g = v * y, h = 0.5 * y;
     double r = fma(-g, h, 0.5);
@@ -198,12 +197,17 @@ __device__ __forceinline__ double sqrt_near(double v)
 
 __device__ __forceinline__ double recip_near(double v)
 {
-    if (!(v >= 0x1p-900 && v <= 0x1p900)) return 1.0 / v;  // uniform
     double r = __builtin_amdgcn_rcp(v);
     r = fma(r, fma(-v, r, 1.0), r);
     r = fma(r, fma(-v, r, 1.0), r);
     return fma(r, fma(-v, r, 1.0), r);
 }
+
+// a column with at most this much below its subdiagonal entry (squared) counts
+// as reduced.  The entries of a Gram matrix of fp32 data lie between 2^-300
+// and 2^300 in magnitude (zeros apart), so that leaving out entries below
+// 2^-450 changes no eigenvalue that doubles can hold beside them
+constexpr double TAIL_MIN = 0x1p-900;
 
 __host__ __device__ constexpr int tg_dots(int q) { return q <= 2 ? 1 : q <= 4 ? 2 : 4; }
 
@@ -337,7 +341,7 @@ __global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32
 #pragma unroll
         for (int v = 0; v < WV; ++v) tail += sm.redt[v];
         const double x0 = sm.x0;
-        const bool live = tail > 0.0;
+        const bool live = tail > TAIL_MIN;
         const double norm = sqrt_near(x0 * x0 + tail);
         const double alpha = (x0 >= 0.0) ? -norm : norm;
         const double u0 = live ? x0 - alpha : 0.0;
@@ -566,6 +570,183 @@ __global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32
     }
 }
 
+// One workgroup of W waves per matrix, for sides up to min(W R, 64 C): lane l
+// of every wave holds columns l, l + 64, ..., wave h the rows h, h + W, ... of
+// them, all in registers.  Every wave keeps the step's vectors whole (entry c
+// in lane c % 64), takes the rows' entries of them as scalars, and derives the
+// step's scalars by itself, so a step has one barrier: for the waves' parts of
+// A u, and row k + 1, through LDS.  The update with (u, w) and the products
+// with the next reflector are one pass over the rows.
+//
+// What bounds it: instruction issue, one wave a SIMD: six lane reads and 3 C
+// multiply-adds a row, and about 250 instructions for the rest of a step.
+// Measured for the 192 matrices (sides 32 and 128) of 64 tensors [32, 128,
+// 128]: 169 us, against 358 us for the matrix in LDS, eight waves and three
+// barriers a step (187 us with range checks around the square root and the
+// reciprocal, and the form stored entry by entry).
+template <int W, int C>
+struct OneShared {
+    double part[2][W][64 * C];
+    double row[2][64 * C];
+};
+
+// entry `at` (uniform) of a vector held C to a lane
+template <int C>
+__device__ __forceinline__ double entry_at(const double (&v)[C], int at)
+{
+    double s = lane_value(v[0], at & 63);
+#pragma unroll
+    for (int c = 1; c < C; ++c)
+        if (at >> 6 == c) s = lane_value(v[c], at & 63);
+    return s;
+}
+
+template <int W, int R, int C>
+__device__ void tri_one(const double* A, int n, double* d, double* e2, OneShared<W, C>& sm)
+{
+    static_assert((64 * C) % (4 * W) == 0 && R % 4 == 0, "rows and lanes");
+    const int lane = threadIdx.x & 63;
+    const int h = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    double a[R][C];
+    double x[C], u[C], w[C], un[C], y[C];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int j = r * W + h;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = lane + 64 * c;
+            a[r][c] = (j < n && col < n) ? A[(size_t)j * n + col] : 0.0;
+        }
+    }
+    double tail = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int col = lane + 64 * c;
+        x[c] = col < n ? A[col] : 0.0;
+        u[c] = w[c] = 0.0;
+        if (col >= 2) tail += x[c] * x[c];
+    }
+    double dv[C], ev[C];  // the form's entries c, in their lanes
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        dv[c] = x[c];
+        ev[c] = 0.0;
+    }
+    for (int k = 0; k + 1 < n; ++k) {
+        // ---- the reflector of column k, from x: row k after step k - 1 (the last
+        // step's is zero: its tail is)
+        tail = wave_total1(tail);
+        const double x0 = entry_at(x, k + 1);
+        const bool live = tail > TAIL_MIN;
+        const double norm = sqrt_near(x0 * x0 + tail);
+        const double alpha = (x0 >= 0.0) ? -norm : norm;
+        const double u0 = live ? x0 - alpha : 0.0;
+        const double beta = live ? 2.0 * recip_near(u0 * u0 + tail) : 0.0;
+        const double off = live ? alpha * alpha : x0 * x0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = lane + 64 * c;
+            ev[c] = (col == k) ? off : ev[c];
+            un[c] = (col == k + 1) ? u0 : (live && col > k + 1) ? x[c] : 0.0;
+            y[c] = 0.0;
+        }
+        // ---- the update of step k - 1 and the products with u
+        const int i0 = (k + W - h) / W;  // rows r >= i0 are matrix rows > k
+#pragma unroll
+        for (int g = 0; g < R; g += 4) {
+            if (g + 4 <= i0) continue;
+#pragma unroll
+            for (int r = g; r < g + 4; ++r) {
+                // row r W + h: lane (r W + h) % 64 of entry r W / 64
+                const int vc = r * W / 64, l = r * W % 64 + h;
+                const double ui = lane_value(u[vc], l), wi = lane_value(w[vc], l);
+                const double ni = lane_value(un[vc], l);
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    a[r][c] = fma(-ui, w[c], fma(-wi, u[c], a[r][c]));
+                    y[c] = fma(a[r][c], ni, y[c]);
+                }
+            }
+        }
+        const int buf = k & 1;
+#pragma unroll
+        for (int c = 0; c < C; ++c) sm.part[buf][h][lane + 64 * c] = y[c];
+        if ((k + 1) % W == h) {
+            const int i = (k + 1) / W;
+#pragma unroll
+            for (int g = 0; g < R; g += 4) {
+                if (i >> 2 != g >> 2) continue;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    double v = a[g][c];
+#pragma unroll
+                    for (int r = 1; r < 4; ++r)
+                        if ((i & 3) == r) v = a[g + r][c];
+                    sm.row[buf][lane + 64 * c] = v;
+                }
+            }
+        }
+        __syncthreads();
+        double dot = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            double s = 0.0;
+#pragma unroll
+            for (int v = 0; v < W; ++v) s += sm.part[buf][v][lane + 64 * c];
+            x[c] = sm.row[buf][lane + 64 * c];
+            u[c] = un[c];
+            w[c] = beta * s;
+            dot = fma(w[c], un[c], dot);
+        }
+        // ---- w = p - K u, and row k + 1 after this step
+        const double K2 = 0.5 * beta * wave_total1(dot);
+        const double w0 = fma(-K2, u0, entry_at(w, k + 1));
+        tail = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = lane + 64 * c;
+            w[c] = col > k ? fma(-K2, u[c], w[c]) : 0.0;
+            x[c] -= fma(u0, w[c], w0 * u[c]);
+            if (col > k + 2) tail += x[c] * x[c];
+            dv[c] = (col == k + 1) ? x[c] : dv[c];
+        }
+    }
+    if (h == 0) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = lane + 64 * c;
+            if (col < n) d[col] = dv[c];
+            if (col + 1 < n) e2[col] = ev[c];
+        }
+    }
+}
+
+// sides up to 128 (four waves), by their own size
+__global__ __launch_bounds__(256) void k_tri_small(const SvdTask* tasks)
+{
+    __shared__ union {
+        OneShared<4, 1> one;
+        OneShared<4, 2> two;
+    } sm;
+    const SvdTask& t = tasks[blockIdx.x];
+    const int n = (int)t.K;
+    if (n <= 32)
+        tri_one<4, 8, 1>(t.gram, n, t.tri, t.tri + n, sm.one);
+    else if (n <= 64)
+        tri_one<4, 16, 1>(t.gram, n, t.tri, t.tri + n, sm.one);
+    else if (n <= TRI_SMALL)
+        tri_one<4, 32, 2>(t.gram, n, t.tri, t.tri + n, sm.two);
+}
+
+// sides up to 192 (eight waves)
+__global__ __launch_bounds__(512) void k_tri_middle(const SvdTask* tasks)
+{
+    __shared__ OneShared<8, 3> sm;
+    const SvdTask& t = tasks[blockIdx.x];
+    const int n = (int)t.K;
+    if (n > TRI_SMALL && n <= TRI_MIDDLE) tri_one<8, 24, 3>(t.gram, n, t.tri, t.tri + n, sm);
+}
+
 // the Gershgorin interval of each tridiagonal form, and the form as the counts
 // read it: scaled by a power of two so that the interval lies within (-1, 1],
 // the pairs {d_i, e2_{i-1}} side by side, padded to whole steps of STURM_STEP
@@ -627,37 +808,25 @@ __global__ __launch_bounds__(PREP_THREADS) void k_tri_prep(const SvdTask* tasks)
 // minors' sequence p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2}, scaled every
 // STURM_STEP terms.  One fused multiply-add separates a term from the next
 // (the ratio of successive terms, which needs no scaling, needs a division
-// there: about 100 cycles a step against about 20).  Each term is exact for
-// a matrix whose d_i - x and e2_{i-1} are off by a few units of rounding, as
-// with the ratios.  The coefficients are the same for every lane: they come
-// by scalar loads, and a step costs five or six vector instructions.
-typedef const __attribute__((address_space(4))) double* cdouble;
+// there).  Each term is exact for a matrix whose d_i - x and e2_{i-1} are off
+// by a few units of rounding, as with the ratios.
+typedef __attribute__((address_space(3))) const double2 lds_pair;
 
-__device__ __forceinline__ int sturm_count(cdouble pairs, int steps, double x)
+__device__ __forceinline__ int sturm_count(lds_pair* pairs, int steps, double x)
 {
     double p = 1.0, pp = 0.0;
     uint32_t signs = 0u;
     int c = 0;
-    double nd[STURM_STEP], ne[STURM_STEP];  // the next step's coefficients (uniform)
-#pragma unroll
-    for (int u = 0; u < STURM_STEP; ++u) {
-        nd[u] = pairs[2 * u];
-        ne[u] = pairs[2 * u + 1];
-    }
-    for (int i = 1; i <= steps; ++i) {
-        double cd[STURM_STEP], ce[STURM_STEP];
-        // (the form is followed by a step's worth of readable doubles)
-        const cdouble at = pairs + 2 * STURM_STEP * (size_t)i;
+    for (int i = 0; i < steps; ++i) {
+        double2 f[STURM_STEP];
 #pragma unroll
         for (int u = 0; u < STURM_STEP; ++u) {
-            cd[u] = nd[u];
-            ce[u] = ne[u];
-            nd[u] = at[2 * u];
-            ne[u] = at[2 * u + 1];
+            f[u].x = pairs[i * STURM_STEP + u].x;
+            f[u].y = pairs[i * STURM_STEP + u].y;
         }
 #pragma unroll
         for (int u = 0; u < STURM_STEP; ++u) {
-            const double np = fma(cd[u] - x, p, -(ce[u] * pp));
+            const double np = fma(f[u].x - x, p, -(f[u].y * pp));
             pp = p;
             p = np;
             signs = __builtin_amdgcn_alignbit(signs, (uint32_t)((uint64_t)__double_as_longlong(p) >> 32), 31);
@@ -674,10 +843,17 @@ __device__ __forceinline__ int sturm_count(cdouble pairs, int steps, double x)
 // power of two): a round counts at G points inside every eigenvalue's
 // interval and keeps the part that holds it, to two units of rounding.
 // Counting at more points at once takes fewer, costlier rounds, so G is just
-// large enough to give every SIMD a wave.  What bounds it: the chain of one
-// fused multiply-add a step, and the issue of five to six instructions.
-__global__ __launch_bounds__(64) void k_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G)
+// large enough to give every SIMD a wave.  What bounds it: the LDS reads of a
+// term's coefficients, the same for every lane, about 16 cycles for each of a
+// CU's waves, then the issue of its five to six instructions.  Measured for
+// 64 tensors [32, 128, 128] and for one side of 4096: 74 us and 1.43 ms; with
+// the coefficients as scalars, requested a group ahead, 78 us and 1.59 ms (in
+// the group that uses them 85 us, 1.95 ms); broadcast from a row of 16 lanes
+// by DPP 83 us, 1.93 ms.
+__global__ __launch_bounds__(STURM_LANES) void k_sturm(const SvdTask* tasks, int n_tasks,
+                                                       int64_t n_items, int G)
 {
+    extern __shared__ double lds_rows[];  // a form's pairs
     const int64_t item = blockIdx.x;
     if (item >= n_items) return;  // uniform
     int lo_t = 0, hi_t = n_tasks - 1;  // the last task whose first item is <= item
@@ -686,23 +862,24 @@ __global__ __launch_bounds__(64) void k_sturm(const SvdTask* tasks, int n_tasks,
         if (tasks[mid].eig0 <= item) lo_t = mid; else hi_t = mid - 1;
     }
     const SvdTask& t = tasks[lo_t];
-    const int n = (int)t.K;
-    const int lane = threadIdx.x;
-    const int steps = tri_padded(n) / STURM_STEP;
-    const cdouble pairs = (cdouble)(const double*)tri_pairs(t.tri, n);
+    const int n = (int)t.K, np = tri_padded(n);
+    const double2* pairs = tri_pairs(t.tri, n);
+    double2* const staged = reinterpret_cast<double2*>(lds_rows);
+    for (int i = threadIdx.x; i < np; i += STURM_LANES) staged[i] = pairs[i];
     const double* b = tri_bounds(t.tri, n);
     double lo = b[0], hi = b[1];
     const int ex = (int)b[2];
-    const int per = 64 / G;
-    // (a group past the last eigenvalue repeats it)
-    const int k = min((int)(item - t.eig0) * per + lane / G, n - 1), g = lane % G;
-    bool done = false;
+    const int per = STURM_LANES / G;
+    // (a group of lanes past the last eigenvalue has nothing to do)
+    const int k = (int)(item - t.eig0) * per + (int)threadIdx.x / G, g = threadIdx.x % G;
+    bool done = k >= n;
+    __syncthreads();
     for (int it = 0; it < 160; ++it) {
         done = done || !(hi - lo > 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 0x1p-148);
         if (__ballot(!done) == 0ull) break;
         const double h = (hi - lo) / (double)(G + 1);
         const double x = lo + h * (double)(g + 1);
-        const int c = sturm_count(pairs, steps, x);
+        const int c = sturm_count((lds_pair*)staged, np / STURM_STEP, x);
         double nlo = lo, nhi = hi;
         if (c <= k) nlo = fmax(nlo, x);
         else nhi = fmin(nhi, x);
@@ -716,7 +893,7 @@ __global__ __launch_bounds__(64) void k_sturm(const SvdTask* tasks, int n_tasks,
             hi = nhi;
         }
     }
-    if (g == 0) t.out[n - 1 - k] = sqrt(ldexp(fmax(0.5 * (lo + hi), 0.0), ex));
+    if (g == 0 && k < n) t.out[n - 1 - k] = sqrt(ldexp(fmax(0.5 * (lo + hi), 0.0), ex));
 }
 
 // how a matrix of side n is spread over a group: rows per member (a multiple
@@ -835,6 +1012,17 @@ hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream
     return hipGetLastError();
 }
 
+hipError_t launch_tri_one(const SvdTask* tasks, int n_tasks, bool small, bool middle,
+                          hipStream_t stream)
+{
+    if (n_tasks <= 0) return hipSuccess;
+    if (small)
+        hipLaunchKernelGGL(k_tri_small, dim3((unsigned)n_tasks), dim3(256), 0, stream, tasks);
+    if (middle)
+        hipLaunchKernelGGL(k_tri_middle, dim3((unsigned)n_tasks), dim3(512), 0, stream, tasks);
+    return hipGetLastError();
+}
+
 int sturm_lanes(int64_t values)
 {
     // enough lanes to give every SIMD of the 256 CUs a wave (no device is
@@ -845,12 +1033,17 @@ int sturm_lanes(int64_t values)
     return G;
 }
 
-hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G, hipStream_t stream)
+hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int G, int n_max,
+                        hipStream_t stream)
 {
     if (n_tasks <= 0) return hipSuccess;
+    const int lds = tri_padded(n_max) * (int)sizeof(double2);
+    hipError_t e = hipFuncSetAttribute((const void*)k_sturm,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tri_prep, dim3((unsigned)n_tasks), dim3(PREP_THREADS), 0, stream, tasks);
-    hipLaunchKernelGGL(k_sturm, dim3((unsigned)n_items), dim3(64), 0, stream, tasks, n_tasks,
-                       n_items, G);
+    hipLaunchKernelGGL(k_sturm, dim3((unsigned)n_items), dim3(STURM_LANES), (size_t)lds, stream,
+                       tasks, n_tasks, n_items, G);
     return hipGetLastError();
 }
 

@@ -193,11 +193,25 @@ def test_large_rank_deficient_unfolding():
     _assert_spectra(got, S.invariants(T), "rank-deficient 700 x 800")
 
 
+# Sides of the one-workgroup classes in registers (32, 64, 128, 192) and their
+# edges, and the smallest matrices
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160, 191, 192])
+def test_register_reduced_sides(K):
+    rng = np.random.default_rng(K)
+    T = rng.standard_normal((K, K + 11)).astype(np.float32)
+    T[K // 2] *= 1e-3
+    if K > 8:
+        T[3] = T[1]  # a rank deficiency
+    log(f"[spectra] register-reduced side {K}")
+    _, _, (got,) = _gpu_lists([T])
+    _assert_spectra(got, S.invariants(T), f"side {K}")
+
+
 # Sides of the group reduction's classes and their edges: the smallest, sides
 # whose rows per member change to fit the slots (489, 505, 1017), whole
 # classes, and one past each (reduced in two classes, one taking over from the
 # other); 3073 and above keep some rows in LDS and in memory
-@pytest.mark.parametrize("K", [129, 130, 257, 489, 505, 512, 513, 1017, 1024, 1025, 2048, 2049])
+@pytest.mark.parametrize("K", [193, 194, 257, 489, 505, 512, 513, 1017, 1024, 1025, 2048, 2049])
 def test_group_reduced_sides(K):
     rng = np.random.default_rng(K)
     T = rng.standard_normal((K, K + 37)).astype(np.float32)
