@@ -10,17 +10,21 @@
 // segment before e_i.
 //
 // Work layout.  One 64-lane wave per chunk of 64 consecutive windows (lane l
-// owns window 64c + l).  Chunk c owns the readings [J_c, J_{c+1}) with
-// J_c = lower_bound(u, s_{64c}), J_0 = 0 and J_C = n: every reading is checked
-// by exactly one wave (the J_c need not even increase for that), and for valid
-// input every endpoint of the chunk's windows has its lower bound in
-// [J_c, J_{c+1}].  The wave streams readings J_c .. min(J_{c+1}, n-1) through
-// LDS in blocks of 256 (4 coalesced loads per lane) and resolves each endpoint
-// by a binary search inside the block that holds its lower bound.  J_c comes
-// from one probe of 64 readings around the position a uniform reading rate
-// predicts, then a 64-ary search when the probe misses (irregular readings).
-// The kernel is bound by HBM bandwidth: it reads every reading and every
-// window once and writes each window's energy and indices once.
+// owns window 64c + l).  For valid input every endpoint of the chunk's windows
+// has its lower bound in [J, K], J = lower_bound(u, first start) and K =
+// lower_bound(u, last end).  Up to CNT_STREAM readings between them are
+// streamed through LDS in blocks of 256 (4 coalesced loads per lane), each
+// endpoint resolved by a binary search inside the block that holds its lower
+// bound; over more (windows far apart: the blocks would follow one another, a
+// memory latency each) every lane searches its two endpoints in memory.  J and
+// K come from one probe of 64 readings around the position a uniform reading
+// rate predicts, then a 64-ary search when the probe misses (irregular
+// readings).  The readings themselves are checked by workgroups of their own,
+// in equal pieces: a chunk's wave that checked the readings up to the next
+// chunk's first one took 130 blocks in a row where the counter was read on for
+// a tenth of the session after its last window (98,304 windows, 340,000
+// readings: 180 us, 9.4 us now).  The kernel is bound by memory latency at the
+// sizes of replay sessions.
 
 #include <hip/hip_ext.h>
 
@@ -33,6 +37,9 @@ constexpr int WAVE = 64;
 constexpr int PER_LANE = CNT_BLOCK / WAVE;  // readings per lane and block
 constexpr int FOLD_THREADS = 256;
 constexpr int CFOLD_BLOCKS = 64;
+constexpr int64_t CNT_STREAM = 16 * CNT_BLOCK;  // most readings a chunk streams
+constexpr int CHECK_PER = 8;  // readings a thread checks
+constexpr int64_t CHECK_BLOCK = (int64_t)CNT_WAVES * WAVE * CHECK_PER;
 
 __device__ __forceinline__ bool finite(double x) { return fabs(x) < INFINITY; }
 
@@ -126,12 +133,63 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t G)
     return (b < 8 * per) ? (b % 8) * per + b / 8 : b;
 }
 
-__global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParams p)
+// readings [blk CHECK_BLOCK, ...): finite, shifted times rising, counter not
+// falling
+__device__ void check_readings(const CounterParams& p, int64_t blk)
+{
+    const int64_t j0 = blk * CHECK_BLOCK + threadIdx.x;
+    constexpr int64_t step = CNT_WAVES * WAVE;
+    uint32_t err = 0u;
+#pragma unroll
+    for (int r = 0; r < CHECK_PER; ++r) {
+        const int64_t j = min(j0 + r * step, p.n - 1);  // (extra lanes repeat the last)
+        const int64_t before = max(j - 1, (int64_t)0);
+        const double t = p.t[j], c = p.C[j];
+        const double u = t - p.delay, ub = p.t[before] - p.delay, cb = p.C[before];
+        const bool first = (j == 0);
+        const bool ok_t = finite(t) && finite(u) && (first || ub < u);
+        const bool ok_c = finite(c) && (first || cb <= c);
+        err |= (ok_t ? 0u : ERR_TIMESTAMPS) | (ok_c ? 0u : ERR_COUNTER);
+    }
+    const uint32_t any = (__ballot((err & ERR_TIMESTAMPS) != 0u) ? ERR_TIMESTAMPS : 0u) |
+                         (__ballot((err & ERR_COUNTER) != 0u) ? ERR_COUNTER : 0u);
+    if (any && threadIdx.x % WAVE == 0) atomicOr(&p.status->err, any);
+}
+
+// the endpoints of a window found in memory: lower bounds in [lo, hi], both
+// searches side by side
+__device__ void search_window(const CounterParams& p, Endpoint& qs, Endpoint& qe, double s,
+                              double e, int64_t lo, int64_t hi)
+{
+    int64_t ls = lo, hs = hi, le = lo, he = hi;
+    while (ls < hs || le < he) {
+        const int64_t ms = (ls + hs) >> 1, me = (le + he) >> 1;
+        const double us = p.t[min(ms, p.n - 1)] - p.delay, ue = p.t[min(me, p.n - 1)] - p.delay;
+        if (ls < hs) {
+            if (us < s) ls = ms + 1; else hs = ms;
+        }
+        if (le < he) {
+            if (ue < e) le = me + 1; else he = me;
+        }
+    }
+    auto fill = [&](Endpoint& q, int64_t a) {
+        const int64_t l = max(a - 1, (int64_t)0), h = min(a, p.n - 1);
+        q = Endpoint{true, a, p.t[l] - p.delay, p.C[l], p.t[h] - p.delay, p.C[h]};
+    };
+    fill(qs, ls);
+    fill(qe, le);
+}
+
+__global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParams p, int64_t nb_win)
 {
     __shared__ double lds_u[CNT_WAVES][CNT_BLOCK + 1];
     __shared__ double lds_c[CNT_WAVES][CNT_BLOCK + 1];
+    if ((int64_t)blockIdx.x >= nb_win) {
+        check_readings(p, (int64_t)blockIdx.x - nb_win);
+        return;
+    }
     const int w = threadIdx.x / WAVE, k = threadIdx.x % WAVE;
-    const int64_t chunk = xcd_block(blockIdx.x, gridDim.x) * CNT_WAVES + w;
+    const int64_t chunk = xcd_block(blockIdx.x, nb_win) * CNT_WAVES + w;
     if (chunk >= p.nchunks) return;  // the whole wave
     double* su = lds_u[w];
     double* sc = lds_c[w];
@@ -144,8 +202,11 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
     const bool has_next = i0 + CNT_CHUNK < m;
     const double s_next = has_next ? p.s[i0 + CNT_CHUNK] : 0.0;
     const double u0 = p.t[0] - p.delay, un = p.t[n - 1] - p.delay;
-    const int64_t Jc = (chunk == 0 || m == 0) ? 0 : wave_lower_bound(p, p.s[i0], u0, un);
-    const int64_t Jn = has_next ? wave_lower_bound(p, s_next, u0, un) : n;
+    int64_t Jc = 0, last = -1;  // readings Jc .. last hold the chunk's endpoints
+    if (i0 < m) {
+        Jc = wave_lower_bound(p, p.s[i0], u0, un);
+        last = min(wave_lower_bound(p, p.e[min(i0 + CNT_CHUNK, m) - 1], u0, un), n - 1);
+    }
 
     uint32_t err = 0u;
     const double s_down = __shfl_down(s, 1);  // all lanes take part
@@ -156,8 +217,13 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
         if (!ok) err |= ERR_INTERVAL;
     }
 
-    // the reading before the chunk's first one (slot 0)
+    Endpoint qs{!live, 0, 0.0, 0.0, 0.0, 0.0}, qe{!live, 0, 0.0, 0.0, 0.0, 0.0};
     double lastu = -INFINITY, lastc = 0.0;
+    if (last - Jc >= CNT_STREAM) {  // uniform
+        if (live) search_window(p, qs, qe, s, e, Jc, last + 1);
+        last = Jc - 1;
+    }
+    // the reading before the chunk's first one (slot 0)
     if (Jc > 0) {
         lastu = p.t[Jc - 1] - p.delay;
         lastc = p.C[Jc - 1];
@@ -167,8 +233,6 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
         sc[0] = lastc;
     }
     __builtin_amdgcn_wave_barrier();
-    Endpoint qs{!live, 0, 0.0, 0.0, 0.0, 0.0}, qe{!live, 0, 0.0, 0.0, 0.0, 0.0};
-    const int64_t last = min(Jn, n - 1);  // last reading streamed
     for (int64_t b = Jc; b <= last; b += CNT_BLOCK) {
         const int cnt = (int)min((int64_t)CNT_BLOCK, last + 1 - b);
         double tv[PER_LANE], cv[PER_LANE];
@@ -189,20 +253,6 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
         // the lanes read each other's slots: keep the compiler from moving
         // those reads above the writes (one wave's LDS operations run in order)
         __builtin_amdgcn_wave_barrier();
-        if (p.validate) {
-#pragma unroll
-            for (int r = 0; r < PER_LANE; ++r) {
-                const int q = k + WAVE * r;
-                const int64_t j = b + q;
-                if (q < cnt && j < Jn) {
-                    const double uq = tv[r] - p.delay;
-                    const bool first = (j == 0);
-                    const bool ok_t = finite(tv[r]) && finite(uq) && (first || su[q] < uq);
-                    const bool ok_c = finite(cv[r]) && (first || sc[q] <= cv[r]);
-                    err |= (ok_t ? 0u : ERR_TIMESTAMPS) | (ok_c ? 0u : ERR_COUNTER);
-                }
-            }
-        }
         const double ulast = su[cnt];
         resolve(qs, s, b, cnt, ulast, su, sc);
         resolve(qe, e, b, cnt, ulast, su, sc);
@@ -229,9 +279,7 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
     const int clipped = count_true(live && (s < u0 || e > un));
 #pragma unroll
     for (int off = WAVE / 2; off > 0; off >>= 1) inc += __shfl_xor(inc, off);
-    const uint32_t any = (__ballot((err & ERR_TIMESTAMPS) != 0u) ? ERR_TIMESTAMPS : 0u) |
-                         (__ballot((err & ERR_COUNTER) != 0u) ? ERR_COUNTER : 0u) |
-                         (__ballot((err & ERR_INTERVAL) != 0u) ? ERR_INTERVAL : 0u);
+    const uint32_t any = __ballot((err & ERR_INTERVAL) != 0u) ? ERR_INTERVAL : 0u;
     if (k == 0) {
         p.part[chunk] = make_double2(inc, (double)clipped);
         if (any) atomicOr(&p.status->err, any);
@@ -290,12 +338,15 @@ __global__ __launch_bounds__(FOLD_THREADS) void k_counter_fold(const CounterPara
 hipError_t launch_counter(const CounterParams& p, hipStream_t stream, hipEvent_t ev_start,
                           hipEvent_t ev_stop)
 {
-    const int64_t blocks = (p.nchunks + CNT_WAVES - 1) / CNT_WAVES;
+    // workgroups of windows, then (when the input is checked) of readings
+    const int64_t nb_win = (p.nchunks + CNT_WAVES - 1) / CNT_WAVES;
+    const int64_t blocks = nb_win + (p.validate ? (p.n + CHECK_BLOCK - 1) / CHECK_BLOCK : 0);
     if (ev_start || ev_stop)
         hipExtLaunchKernelGGL(k_counter, dim3((unsigned)blocks), dim3(CNT_WAVES * WAVE), 0, stream,
-                              ev_start, ev_stop, 0, p);
+                              ev_start, ev_stop, 0, p, nb_win);
     else
-        hipLaunchKernelGGL(k_counter, dim3((unsigned)blocks), dim3(CNT_WAVES * WAVE), 0, stream, p);
+        hipLaunchKernelGGL(k_counter, dim3((unsigned)blocks), dim3(CNT_WAVES * WAVE), 0, stream, p,
+                           nb_win);
     return hipGetLastError();
 }
 

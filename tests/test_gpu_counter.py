@@ -184,3 +184,37 @@ def test_asynchronous_and_timed_calls_equal_the_synchronous_one():
                         "latency")
     assert got[2]["n_clipped"] == ref[2]["n_clipped"]
     assert got[2]["kernel_ms"] > 0.0 and got[2]["device_ms"] >= got[2]["kernel_ms"]
+
+
+# windows so far apart that a chunk of 64 spans more than the 4,096 readings it
+# would stream (each endpoint is then searched in memory), spans around that
+# limit, readings long before the first and after the last window, and the
+# edges of the pieces in which readings are checked (2,048)
+@pytest.mark.parametrize("n,m", [(4096, 40), (4097, 40), (4200, 64), (5000, 64), (60000, 3),
+                                 (100_000, 150), (2047, 5), (2048, 5), (2049, 5), (6145, 1)])
+def test_sparse_windows_and_unwatched_readings(n, m):
+    c = synth.counter_case(8100 + n + m, n=n, m=m, outside=n % 2 == 0)
+    compare(c, f"sparse n{n} m{m}")
+    c = synth.counter_case(8200 + n + m, n=n, m=m, irregular=True)
+    compare(c, f"sparse irregular n{n} m{m}")
+    # every window inside a short stretch: most readings lie outside it
+    c = synth.counter_case(8300 + n + m, n=n, m=m, outside=False)
+    lo, span = c["t"][0], c["t"][-1] - c["t"][0]
+    for k in ("s", "e"):
+        c[k] = lo + 0.4 * span + (c[k] - lo) * 0.01
+    compare(c, f"clustered n{n} m{m}")
+
+
+@pytest.mark.parametrize("j", [0, 1, 2047, 2048, 5999])
+def test_bad_reading_anywhere(j):
+    """A reading far from every window is checked all the same."""
+    import paper_2512_08365_amd as mag
+    c = synth.counter_case(8400, n=6000, m=4, outside=False, delay=0.0)
+    for name, value, code in (("C", np.nan, -13), ("t", np.nan, -5)):
+        d = {k: np.array(c[k]) for k in c if isinstance(c[k], np.ndarray)}
+        d["reps"] = c["reps"]
+        d[name][j] = value
+        g = _dev(d)
+        with pytest.raises(mag.MagnetonError) as err:
+            mag.attribute_counter(g["t"], g["C"], g["s"], g["e"], g["key"], replays=g["reps"])
+        assert err.value.code in ((code,) if name == "C" else (code, -7)), (name, j)
