@@ -29,28 +29,75 @@ __device__ __forceinline__ double endpoint_x(const double* s, const double* e, i
 // ---------------------------------------------------------------------------
 namespace {
 
+// An interval that is active at the start of tiles b, b + 1, ... takes its
+// pieces of them, in batches of FIX_BATCH tiles whose loads are requested
+// together; beyond the first batch the wave takes its long intervals one
+// after the other, 64 tiles at a time (walked by one thread, tile after tile, an
+// interval of 40 tiles waited for 40 memory latencies in a row: 1,000
+// intervals of 0.15 s over 7.65 M samples at 100 kHz 67 us, now 8 us).  The
+// pieces are added in a fixed order: the batch in tile order, then the rest
+// lane by lane.
+constexpr int FIX_BATCH = 8;
+
 __device__ void fix_cross(const FixParams& p, int64_t idx)
 {
     const int64_t NT = p.NT, LD = p.ld;
-    const int a = (int)(idx / (NT + 1));
-    const int64_t b = idx - (int64_t)a * (NT + 1);
+    const bool in = idx < (int64_t)p.ss.S * (NT + 1);
+    const int a = in ? (int)(idx / (NT + 1)) : 0;
+    const int64_t b = in ? idx - (int64_t)a * (NT + 1) : 0;
     const int64_t* c = p.cnt + (int64_t)a * (LD + 1);
     // the three loads requested together
     const int64_t c0 = c[b];
     const int64_t cprev = (b > 0) ? c[b - 1] : -1;
     const int64_t fin = p.cnt_fin[(int64_t)a * (LD + 1) + b];
     const int64_t len = 2 * (p.ss.off[a + 1] - p.ss.off[a]);
-    if (p.validate && b > 0 && b < NT && fin != CNT_UNSET && fin != c0) {
+    if (in && p.validate && b > 0 && b < NT && fin != CNT_UNSET && fin != c0) {
         // a wave stopped at tile b with a cursor other than the one the next
         // wave searched for: some stream is unsorted
         atomicOr(&p.status->err, ERR_INTERVAL);
     }
-    if (!(c0 & 1) || c0 > len) return;         // no interval active at tile start
-    if (cprev == c0) return;                   // not the first tile it is active at
-    const int64_t gid = p.ss.off[a] + (c0 >> 1);
-    double E = (b > 0) ? p.tail[(int64_t)a * LD + b - 1] : 0.0;
-    for (int64_t bb = b; bb < NT && c[bb] == c0; ++bb) E += p.head[(int64_t)a * LD + bb];
-    p.energy[gid] = E;
+    // an interval is active at the tile's start, and this is the first such tile
+    const bool mine = in && (c0 & 1) && c0 <= len && cprev != c0;
+    if (__ballot(mine) == 0ull) return;
+    double E = 0.0;
+    bool more = false;  // the interval goes on past the batch
+    if (mine) {
+        const double* head = p.head + (int64_t)a * LD;
+        E = (b > 0) ? p.tail[(int64_t)a * LD + b - 1] : 0.0;
+        int64_t cv[FIX_BATCH];
+        double hv[FIX_BATCH];
+#pragma unroll
+        for (int u = 0; u < FIX_BATCH; ++u) {
+            const int64_t bb = min(b + u, NT - 1);
+            cv[u] = c[bb];
+            hv[u] = head[bb];
+        }
+        more = true;
+#pragma unroll
+        for (int u = 0; u < FIX_BATCH; ++u) {
+            more = more && b + u < NT && cv[u] == c0;
+            if (more) E += hv[u];
+        }
+    }
+    for (uint64_t left = __ballot(more); left != 0ull; left &= left - 1ull) {
+        const int l = (int)__builtin_ctzll(left);
+        const int la = __shfl(a, l);
+        const int64_t lb = __shfl(b, l), lc = __shfl(c0, l);
+        const int64_t* cr = p.cnt + (int64_t)la * (LD + 1);
+        const double* hr = p.head + (int64_t)la * LD;
+        double v = 0.0;
+        for (int64_t b1 = lb + FIX_BATCH; b1 < NT; b1 += 64) {
+            const int64_t bb = b1 + (threadIdx.x & 63);
+            const int64_t cb = cr[min(bb, NT - 1)];
+            const double hb = hr[min(bb, NT - 1)];
+            const bool on = bb < NT && cb == lc;
+            v += on ? hb : 0.0;
+            if (__ballot(on) != ~0ull) break;  // (cursors rise: the last tiles)
+        }
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if ((int)(threadIdx.x & 63) == l) E += v;
+    }
+    if (mine) p.energy[p.ss.off[a] + (c0 >> 1)] = E;
 }
 
 // endpoints of stream a before t_0 / after t_{n-1}: thread r of nthreads
@@ -138,8 +185,7 @@ __global__ __launch_bounds__(FIX_THREADS) void k_fix(const FixParams p, int64_t 
 {
     const int64_t blk = blockIdx.x;
     if (blk < nb_cross) {
-        const int64_t idx = blk * FIX_THREADS + threadIdx.x;
-        if (idx < (int64_t)p.ss.S * (p.NT + 1)) fix_cross(p, idx);
+        fix_cross(p, blk * FIX_THREADS + threadIdx.x);  // (whole waves)
         return;
     }
     const int64_t bo = blk - nb_cross;
