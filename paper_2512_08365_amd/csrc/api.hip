@@ -554,7 +554,7 @@ struct Job {
         fp.part = w.part;
         fp.fold = w.fold;
         fp.validate = validate() ? 1 : 0;
-        if (grouping && pl.m > 0 && pl.H > 0 && !pl.ext_keys) {
+        if (grouping && pl.m > mag::GROUP_SMALL && pl.H > 0 && !pl.ext_keys) {
             fp.table = w.table;
             fp.H = pl.H;
             fp.urank = w.urank;
@@ -1013,7 +1013,7 @@ int mag_attribute_counter(const double* timestamps, const double* counter, int64
     cp.part = job.w.part;
     cp.status = job.w.status;
     cp.validate = job.validate() ? 1 : 0;
-    if (per_key && n_intervals > 0 && job.pl.H > 0) {
+    if (per_key && n_intervals > mag::GROUP_SMALL && job.pl.H > 0) {
         cp.table = job.w.table;
         cp.H = job.pl.H;
         cp.urank = job.w.urank;

@@ -25,6 +25,7 @@ constexpr int MAX_STREAMS = MAG_MAX_STREAMS;
 constexpr int AGG_THREADS = 1024;
 constexpr int AGG_IDS = 8192;       // key ids per LDS table (count u32 + sum f64)
 constexpr int AGG_MAX_CHUNKS = 256; // interval chunks (partial tables)
+constexpr int GROUP_SMALL = 4096;   // intervals that one workgroup groups by itself
 
 // workgroups of k_fix that add up the per-run trace and idle energies; each
 // leaves its partial sum in a fold array that the call's last kernel adds up

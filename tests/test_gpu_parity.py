@@ -68,6 +68,32 @@ def test_intervals_spanning_many_tiles(streams):
         compare_attribution(c, label=f"long s{streams} n{n} per{per}")
 
 
+# intervals over so many tiles that their pieces come in one batch (up to 8), in
+# a batch and a wave's pass of 64, or in several passes; one beyond each edge
+@pytest.mark.parametrize("streams,split", [(1, True), (3, True), (3, False)])
+def test_pieces_of_long_intervals(streams, split):
+    rng = np.random.default_rng(77 + streams)
+    T = 512
+    spans = [1, 2, 7, 8, 9, 10, 63, 64, 65, 71, 72, 73, 74, 136, 137, 200]
+    n = (sum(spans) + 3 * len(spans)) * T + 17
+    t = np.concatenate([[0.0], np.cumsum(rng.uniform(0.5, 1.5, n - 1))]) * 1e-6
+    P = rng.uniform(50.0, 800.0, n).astype(np.float32)
+    s, e, off = [], [], [0]
+    for a in range(streams):
+        at = 5 + 31 * a
+        order = list(spans) if a == 0 else list(rng.permutation(spans))
+        for k in order:
+            s.append(t[at] + 1e-8)
+            at += k * T
+            e.append(t[at] - 1e-8)
+            at += T + 100
+        off.append(len(s))
+    key = rng.integers(0, 5, len(s)).astype(np.uint64)
+    c = {"t": t, "P": P, "s": np.array(s), "e": np.array(e), "key": key,
+         "offsets": np.array(off, np.int64)}
+    compare_attribution(c, equal_split=split, label=f"long pieces S{streams} split{split}")
+
+
 def test_dense_endpoints_force_rounds():
     # thousands of endpoints inside one tile (and inside single segments)
     rng = np.random.default_rng(3)
@@ -139,6 +165,30 @@ def test_degenerate_cases():
         c = {"t": t, "P": P, "s": s, "e": e, "key": np.arange(s.shape[0]).astype(np.uint64),
              "offsets": np.array([0, s.shape[0]])}
         compare_attribution(c, label=name)
+
+
+# the one-workgroup grouping (up to 4,096 intervals) and the sizes next to it:
+# ranks by counting (up to 256 keys) and by sorting, keys 0 and 2^64 - 1, a
+# capacity equal to the key count
+@pytest.mark.parametrize("m,keys", [(1, 1), (2, 2), (63, 1), (64, 64), (255, 255), (256, 256),
+                                    (257, 257), (1000, 300), (2049, 513), (4095, 4095),
+                                    (4096, 4096), (4096, 2), (4097, 4097), (5000, 70)])
+def test_small_groupings(m, keys):
+    rng = np.random.default_rng(m * 7 + keys)
+    n = 3 * m + 50
+    t = np.concatenate([[0.0], np.cumsum(rng.uniform(0.5, 1.5, n - 1))])
+    P = rng.uniform(0.0, 500.0, n).astype(np.float32)
+    cuts = np.sort(rng.uniform(t[0], t[-1], 2 * m))
+    vocab = rng.integers(0, 2**63, keys, dtype=np.int64).astype(np.uint64) * np.uint64(2)
+    vocab[0] = np.uint64(0)
+    if keys > 1:
+        vocab[1] = np.uint64(2**64 - 1)
+    vocab = np.unique(vocab)
+    idx = rng.permutation(np.concatenate([np.arange(len(vocab)),
+                                          rng.integers(0, len(vocab), m - len(vocab))]))
+    c = {"t": t, "P": P, "s": cuts[0::2].copy(), "e": cuts[1::2].copy(), "key": vocab[idx],
+         "offsets": np.array([0, m], np.int64)}
+    compare_attribution(c, key_capacity=len(vocab), label=f"small grouping m{m} keys{keys}")
 
 
 def test_extreme_keys():
