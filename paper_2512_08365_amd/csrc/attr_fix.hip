@@ -34,7 +34,7 @@ namespace {
 // together; beyond the first batch the wave takes its long intervals one
 // after the other, 64 tiles at a time (walked by one thread, tile after tile, an
 // interval of 40 tiles waited for 40 memory latencies in a row: 1,000
-// intervals of 0.15 s over 7.65 M samples at 100 kHz 67 us, now 8 us).  The
+// intervals of 0.15 s over 7.65 M samples at 100 kHz 67 us, now 6.3 us).  The
 // pieces are added in a fixed order: the batch in tile order, then the rest
 // lane by lane.
 constexpr int FIX_BATCH = 8;

@@ -143,7 +143,8 @@ constexpr int INS_CHUNK = 2048;
 constexpr int INS_SLOTS = 4096;
 constexpr int INS_GROUPS = 128;  // the lookup pass inserts keys first seen later
 constexpr int INS_PER = INS_CHUNK / INS_THREADS;
-constexpr int INS_SPT = INS_SLOTS / INS_THREADS;
+constexpr uint32_t INS_ROUNDS = 4;
+constexpr int INS_RPT = INS_SLOTS / INS_THREADS / INS_ROUNDS;  // LDS slots of a thread and round
 
 __global__ __launch_bounds__(INS_THREADS) void k_key_insert(const GroupParams p, int64_t n_insert)
 {
@@ -178,42 +179,51 @@ __global__ __launch_bounds__(INS_THREADS) void k_key_insert(const GroupParams p,
     if (special) atomicOr(&p.kstat->special, 1u);
     __syncthreads();
 
+    // the LDS slots in INS_ROUNDS parts, each workgroup starting with another
+    // one: a key that another workgroup has inserted meanwhile costs a load, not
+    // a swap, and swaps into one line take turns (416 keys in 2,048 slots from
+    // 48 workgroups: 19.3 us all at once, 13.3 us)
     const uint32_t mask = p.H - 1u;
-    unsigned long long key[INS_SPT];
-    uint32_t h[INS_SPT];
     uint32_t pending = 0u;
+    for (uint32_t round = 0; round < INS_ROUNDS; ++round) {
+        const uint32_t part = (round + blockIdx.x) % INS_ROUNDS;
+        unsigned long long key[INS_RPT];
+        uint32_t h[INS_RPT];
+        pending = 0u;
 #pragma unroll
-    for (int u = 0; u < INS_SPT; ++u) {
-        key[u] = lt[tid + u * INS_THREADS];
-        h[u] = (uint32_t)fmix64(key[u]) & mask;
-        if (key[u] != EMPTY_KEY) pending |= 1u << u;
-    }
-    for (uint32_t probe = 0; pending != 0u && probe < p.H; ++probe) {
-        // device-coherent loads (the level-2 caches of the XCDs are not
-        // coherent with each other, so a plain load could keep returning a
-        // stale empty slot and force a swap per probe); a slot only ever
-        // changes from empty to its final key, so a non-empty value is final
-        unsigned long long cur[INS_SPT];
-#pragma unroll
-        for (int u = 0; u < INS_SPT; ++u)
-            cur[u] = ((pending >> u) & 1u)
-                         ? __hip_atomic_load(slot_key(p, h[u]), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT)
-                         : 0ull;
-        unsigned long long old[INS_SPT];
-#pragma unroll
-        for (int u = 0; u < INS_SPT; ++u)
-            old[u] = (((pending >> u) & 1u) && cur[u] == EMPTY_KEY)
-                         ? atomicCAS(slot_key(p, h[u]), EMPTY_KEY, key[u])
-                         : cur[u];
-#pragma unroll
-        for (int u = 0; u < INS_SPT; ++u) {
-            if (!((pending >> u) & 1u)) continue;
-            if (old[u] == key[u] || (cur[u] == EMPTY_KEY && old[u] == EMPTY_KEY))
-                pending &= ~(1u << u);
-            else
-                h[u] = (h[u] + 1u) & mask;
+        for (int u = 0; u < INS_RPT; ++u) {
+            key[u] = lt[tid + (part * INS_RPT + u) * INS_THREADS];
+            h[u] = (uint32_t)fmix64(key[u]) & mask;
+            if (key[u] != EMPTY_KEY) pending |= 1u << u;
         }
+        for (uint32_t probe = 0; pending != 0u && probe < p.H; ++probe) {
+            // device-coherent loads (the level-2 caches of the XCDs are not
+            // coherent with each other, so a plain load could keep returning a
+            // stale empty slot and force a swap per probe); a slot only ever
+            // changes from empty to its final key, so a non-empty value is final
+            unsigned long long cur[INS_RPT];
+#pragma unroll
+            for (int u = 0; u < INS_RPT; ++u)
+                cur[u] = ((pending >> u) & 1u)
+                             ? __hip_atomic_load(slot_key(p, h[u]), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)
+                             : 0ull;
+            unsigned long long old[INS_RPT];
+#pragma unroll
+            for (int u = 0; u < INS_RPT; ++u)
+                old[u] = (((pending >> u) & 1u) && cur[u] == EMPTY_KEY)
+                             ? atomicCAS(slot_key(p, h[u]), EMPTY_KEY, key[u])
+                             : cur[u];
+#pragma unroll
+            for (int u = 0; u < INS_RPT; ++u) {
+                if (!((pending >> u) & 1u)) continue;
+                if (old[u] == key[u] || (cur[u] == EMPTY_KEY && old[u] == EMPTY_KEY))
+                    pending &= ~(1u << u);
+                else
+                    h[u] = (h[u] + 1u) & mask;
+            }
+        }
+        if (pending) break;  // the table is full
     }
     if (pending) atomicOr(&p.kstat->overflow, 1u);
 }
@@ -380,6 +390,11 @@ __global__ __launch_bounds__(RANK_TILE) void k_rank(const GroupParams p)
 
 // intervals per thread whose loads are requested together
 constexpr int AGG_BATCH = 16;
+// a call of at most this many intervals has every key inserted by k_key_insert
+constexpr int64_t PREFIX_ALL = (int64_t)INS_CHUNK * INS_GROUPS;
+// (its chunks have 4,096 intervals)
+constexpr int AGG_PER_LOOKUP = 4;
+static_assert((PREFIX_ALL + 4095) / 4096 <= AGG_MAX_CHUNKS, "chunks of 4,096 intervals");
 
 // chunk of intervals -> LDS table over ids [r0, r0 + SUM_IDS) -> partial table
 // row.  Its 12 bytes per id fit 12,288 ids in 144 KiB of LDS, so a chunk is
@@ -564,6 +579,22 @@ __global__ __launch_bounds__(FIN_KEYS * FIN_GROUPS) void k_fin_m2(const GroupPar
 
 // count, sum and M2 about the chunk's own mean, per id of one chunk held in
 // registers (the chunk is at most AGG_THREADS * AGG_BATCH intervals)
+// LOOKUP: the ids come from the key table itself (every key is in it: at most
+// PREFIX_ALL intervals), so neither k_keymap nor a second k_compact runs
+__device__ __forceinline__ uint32_t table_id(const GroupParams& p, unsigned long long k,
+                                             uint32_t h, ulonglong2 e)
+{
+    if (k == EMPTY_KEY) return (uint32_t)slot_load(p, p.H).y;
+    const uint32_t mask = p.H - 1u;
+    for (uint32_t probe = 0; e.x != k; ++probe) {
+        if (e.x == EMPTY_KEY || probe >= p.H) return NO_ID;  // (the table was full)
+        h = (h + 1u) & mask;
+        e = slot_load(p, h);
+    }
+    return (uint32_t)e.y;
+}
+
+template <bool LOOKUP>
 __global__ __launch_bounds__(AGG_THREADS) void k_agg_one(const GroupParams p)
 {
     __shared__ uint32_t lcnt[AGG_IDS];
@@ -577,11 +608,30 @@ __global__ __launch_bounds__(AGG_THREADS) void k_agg_one(const GroupParams p)
     // per interval): its workgroups look at the key count before anything else
     if (blockIdx.y > 0 && r0 >= (int64_t)p.kstat->n_unique) return;  // uniform
     // the loads are requested before the key count is read
+    if constexpr (LOOKUP) {
+        unsigned long long key[AGG_PER_LOOKUP];
 #pragma unroll
-    for (int k = 0; k < AGG_BATCH; ++k) {
-        const int64_t i = lo + threadIdx.x + (int64_t)k * AGG_THREADS;
-        sl[k] = (i < hi) ? p.slot[i] : NO_ID;
-        en[k] = (i < hi) ? p.energy[i] : 0.0;
+        for (int k = 0; k < AGG_BATCH; ++k) {
+            const int64_t i = lo + threadIdx.x + (int64_t)k * AGG_THREADS;
+            if (k < AGG_PER_LOOKUP) key[k] = (i < hi) ? p.keys[i] : 0ull;
+            en[k] = (i < hi) ? p.energy[i] : 0.0;
+            sl[k] = NO_ID;
+        }
+        ulonglong2 e[AGG_PER_LOOKUP];
+#pragma unroll
+        for (int k = 0; k < AGG_PER_LOOKUP; ++k)
+            e[k] = slot_load(p, (uint32_t)fmix64(key[k]) & (p.H - 1u));
+#pragma unroll
+        for (int k = 0; k < AGG_PER_LOOKUP; ++k)
+            if (lo + threadIdx.x + (int64_t)k * AGG_THREADS < hi)
+                sl[k] = table_id(p, key[k], (uint32_t)fmix64(key[k]) & (p.H - 1u), e[k]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < AGG_BATCH; ++k) {
+            const int64_t i = lo + threadIdx.x + (int64_t)k * AGG_THREADS;
+            sl[k] = (i < hi) ? p.slot[i] : NO_ID;
+            en[k] = (i < hi) ? p.energy[i] : 0.0;
+        }
     }
     if (blockIdx.y == 0) {
         // the chunk's total energy (all its intervals, whatever their key)
@@ -602,7 +652,7 @@ __global__ __launch_bounds__(AGG_THREADS) void k_agg_one(const GroupParams p)
     int d[AGG_BATCH];
 #pragma unroll
     for (int k = 0; k < AGG_BATCH; ++k) {
-        const uint32_t id = resolve_id(p, sl[k]);
+        const uint32_t id = LOOKUP ? sl[k] : resolve_id(p, sl[k]);
         const int64_t x = (id == NO_ID) ? -1 : (int64_t)id - r0;
         d[k] = (x < 0 || x >= nid) ? -1 : (int)x;
     }
@@ -684,27 +734,32 @@ __global__ __launch_bounds__(AGG_THREADS) void k_agg_dur(const GroupParams p)
 }
 
 // per key: count and sum over the chunk rows (as k_fin_sum), then
-// M2 = sum_c (M2_c + n_c (mean_c - mean)^2) over the same rows; 32 keys per
-// workgroup, each key's rows split over 32 interleaved groups
-constexpr int FO_KEYS = 32;
-constexpr int FO_GROUPS = 32;
-constexpr unsigned FO_EAGER = 256;
-__global__ __launch_bounds__(FO_KEYS * FO_GROUPS) void k_fin_one(const GroupParams p)
+// M2 = sum_c (M2_c + n_c (mean_c - mean)^2) over the same rows; 16 keys per
+// workgroup, each key's rows split over 64 interleaved groups of threads, whose
+// rows (at most four) are loaded once and kept in registers.  Bound by the
+// latency of those loads and of two reductions: 2,000 keys over 245 chunks
+// 7.0 us, against 16.8 us with 32 keys a workgroup (64 workgroups) and the rows
+// read again for M2.
+constexpr int FO_KEYS = 16;
+constexpr int FO_GROUPS = 64;
+constexpr int FO_THREADS = FO_KEYS * FO_GROUPS;
+constexpr int FO_ROWS = (AGG_MAX_CHUNKS + FO_GROUPS - 1) / FO_GROUPS;
+constexpr unsigned FO_EAGER = 512;
+
+// sum over the lanes of a wave that hold the same key
+__device__ __forceinline__ double key_lanes(double v)
 {
-    if (blockIdx.x == 0) {
-        __shared__ double red[3 * FO_KEYS * FO_GROUPS / 64];
-        write_totals(p, red, FO_KEYS * FO_GROUPS);
-    }
-    if (p.kstat != p.status && blockIdx.x == 0 && threadIdx.x == 0) {
-        // a key plan built beforehand: its counts become the call's
-        p.status->n_unique = p.kstat->n_unique;
-        if (p.kstat->overflow) p.status->overflow = 1u;
-    }
-    __shared__ uint64_t qc[FO_GROUPS][FO_KEYS];
-    __shared__ double qs[FO_GROUPS][FO_KEYS];
-    __shared__ double qmean[FO_KEYS];
-    __shared__ double qdu[FO_GROUPS][FO_KEYS];
-    const int kl = threadIdx.x % FO_KEYS, grp = threadIdx.x / FO_KEYS;
+    for (int off = FO_KEYS; off < 64; off <<= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+__global__ __launch_bounds__(FO_THREADS) void k_fin_one(const GroupParams p)
+{
+    constexpr int WV = FO_THREADS / 64;
+    __shared__ double red[3 * WV];
+    __shared__ uint32_t qc[WV][FO_KEYS];
+    __shared__ double qs[WV][FO_KEYS], qdu[WV][FO_KEYS], qm[WV][FO_KEYS];
+    const int kl = threadIdx.x % FO_KEYS, grp = threadIdx.x / FO_KEYS, wave = threadIdx.x / 64;
     const int64_t id = (int64_t)blockIdx.x * FO_KEYS + kl;
     // the rows of the first FO_EAGER workgroups are requested before the key
     // count is read; the others, often beyond it (a capacity of one row per
@@ -712,18 +767,17 @@ __global__ __launch_bounds__(FO_KEYS * FO_GROUPS) void k_fin_one(const GroupPara
     // 19.7 us with every row requested, 6.6 us)
     if (blockIdx.x >= FO_EAGER && (int64_t)blockIdx.x * FO_KEYS >= (int64_t)p.kstat->n_unique)
         return;  // uniform
-    uint64_t cnt = 0;
-    double sum = 0.0, du = 0.0;
-    if (id < p.cap) {
-#pragma unroll 8
-        for (int c = grp; c < p.nchunks; c += FO_GROUPS) {
-            cnt += p.pcnt[(int64_t)c * p.cap + id];
-            sum += p.psum[(int64_t)c * p.cap + id];
-        }
-    }
-    if (p.dur_out && id < p.cap) {
-#pragma unroll 8
-        for (int c = grp; c < p.nchunks; c += FO_GROUPS) du += p.pdur[(int64_t)c * p.cap + id];
+    uint32_t rc[FO_ROWS];
+    double rs[FO_ROWS], rm[FO_ROWS], du = 0.0;
+#pragma unroll
+    for (int u = 0; u < FO_ROWS; ++u) {
+        const int c = grp + u * FO_GROUPS;
+        const bool in = c < p.nchunks && id < p.cap;
+        const int64_t at = in ? (int64_t)c * p.cap + id : 0;
+        rc[u] = in ? p.pcnt[at] : 0u;
+        rs[u] = in ? p.psum[at] : 0.0;
+        rm[u] = in ? p.pm2[at] : 0.0;
+        if (p.dur_out && in) du += p.pdur[at];
     }
     uint32_t r = 0xffffffffu;
     uint64_t key = 0;
@@ -733,52 +787,62 @@ __global__ __launch_bounds__(FO_KEYS * FO_GROUPS) void k_fin_one(const GroupPara
     }
     const int64_t nk = min((int64_t)p.kstat->n_unique, p.cap);
     if (p.n_keys_out && blockIdx.x == 0 && threadIdx.x == 0) *p.n_keys_out = nk;
-    if ((int64_t)blockIdx.x * FO_KEYS >= nk) return;  // uniform
-    qc[grp][kl] = cnt;
-    qs[grp][kl] = sum;
-    qdu[grp][kl] = du;
-    __syncthreads();
-    if (grp == 0) {
-        cnt = 0;
-        sum = 0.0;
-        du = 0.0;
-        for (int g = 0; g < FO_GROUPS; ++g) {
-            cnt += qc[g][kl];
-            sum += qs[g][kl];
-            du += qdu[g][kl];
-        }
-        qmean[kl] = cnt ? sum / (double)cnt : 0.0;
-        if (id < nk) {
-            if ((int64_t)r < p.cap) {
-                p.keys_out[r] = key;
-                p.count_out[r] = (int64_t)cnt;
-                p.sum_out[r] = sum;
-                if (p.dur_out) p.dur_out[r] = du;
-            }
-        }
+    if (blockIdx.x > 0 && (int64_t)blockIdx.x * FO_KEYS >= nk) return;  // uniform
+    uint32_t cnt = 0u;
+    double sum = 0.0;
+#pragma unroll
+    for (int u = 0; u < FO_ROWS; ++u) {
+        cnt += rc[u];
+        sum += rs[u];
+    }
+    for (int off = FO_KEYS; off < 64; off <<= 1) cnt += __shfl_xor(cnt, off);
+    sum = key_lanes(sum);
+    du = key_lanes(du);
+    if (threadIdx.x % 64 < FO_KEYS) {
+        qc[wave][kl] = cnt;
+        qs[wave][kl] = sum;
+        qdu[wave][kl] = du;
     }
     __syncthreads();
+    uint64_t n = 0;
+    sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < WV; ++w) {
+        n += qc[w][kl];
+        sum += qs[w][kl];
+    }
+    const double mean = n ? sum / (double)n : 0.0;
     double m2 = 0.0;
-    if (id < nk) {
-        // branch-free, so that the loads of many chunk rows are in flight together
-        const double mean = qmean[kl];
-#pragma unroll 8
-        for (int c = grp; c < p.nchunks; c += FO_GROUPS) {
-            const uint32_t nc = p.pcnt[(int64_t)c * p.cap + id];
-            const double sc = p.psum[(int64_t)c * p.cap + id];
-            const double mc = p.pm2[(int64_t)c * p.cap + id];
-            const double dn = (double)nc;
-            const double dm = (nc ? sc / dn : mean) - mean;
-            m2 += mc + dn * dm * dm;
-        }
+#pragma unroll
+    for (int u = 0; u < FO_ROWS; ++u) {
+        const double dn = (double)rc[u];
+        const double dm = (rc[u] ? rs[u] / dn : mean) - mean;
+        m2 += rm[u] + dn * dm * dm;
     }
+    m2 = key_lanes(m2);
+    if (threadIdx.x % 64 < FO_KEYS) qm[wave][kl] = m2;
     __syncthreads();
-    qs[grp][kl] = m2;
-    __syncthreads();
-    if (grp == 0 && id < nk) {
+    if (grp == 0 && id < nk && (int64_t)r < p.cap) {
         m2 = 0.0;
-        for (int g = 0; g < FO_GROUPS; ++g) m2 += qs[g][kl];
-        if ((int64_t)r < p.cap) p.m2_out[r] = m2;
+        du = 0.0;
+#pragma unroll
+        for (int w = 0; w < WV; ++w) {
+            m2 += qm[w][kl];
+            du += qdu[w][kl];
+        }
+        p.keys_out[r] = key;
+        p.count_out[r] = (int64_t)n;
+        p.sum_out[r] = sum;
+        p.m2_out[r] = m2;
+        if (p.dur_out) p.dur_out[r] = du;
+    }
+    if (blockIdx.x == 0) {
+        write_totals(p, red, FO_THREADS);
+        if (p.kstat != p.status && threadIdx.x == 0) {
+            // a key plan built beforehand: its counts become the call's
+            p.status->n_unique = p.kstat->n_unique;
+            if (p.kstat->overflow) p.status->overflow = 1u;
+        }
     }
 }
 
@@ -786,7 +850,7 @@ __global__ __launch_bounds__(FO_KEYS * FO_GROUPS) void k_fin_one(const GroupPara
 // Up to GS_MAX intervals: the whole grouping by one workgroup, in LDS (the key
 // map, the ranks, count, sum, M2 about the mean, latency, the totals), where
 // seven launches after one another would each cost more than the work: 2,000
-// intervals of 50 keys 32 us in seven kernels, 7 us here.  Bound by the latency
+// intervals of 50 keys 32 us in seven kernels, 12 us here.  Bound by the latency
 // of its LDS passes; above GS_MAX the table would not fit beside the sums.
 // ---------------------------------------------------------------------------
 constexpr int GS_THREADS = 1024;
@@ -1040,7 +1104,8 @@ __global__ __launch_bounds__(256) void k_plan_clear(const GroupParams p)
     }
 }
 
-hipError_t launch_key_map(const GroupParams& p, bool clear, hipStream_t stream)
+// with `ids` every interval's id is recorded too (k_agg_one<true> needs none)
+static hipError_t launch_keys(const GroupParams& p, bool clear, bool ids, hipStream_t stream)
 {
     if (clear) {
         const unsigned cb = (unsigned)min(((int64_t)p.H + 256) / 256, (int64_t)2048);
@@ -1053,12 +1118,15 @@ hipError_t launch_key_map(const GroupParams& p, bool clear, hipStream_t stream)
     const unsigned hb =
         (unsigned)(((int64_t)p.H + 1 + CMP_THREADS * CMP_PER - 1) / (CMP_THREADS * CMP_PER));
     hipLaunchKernelGGL(k_compact, dim3(hb), dim3(CMP_THREADS), 0, stream, p);
-    const int64_t mb =
-        min((p.m + KM_THREADS * KM_BATCH - 1) / (KM_THREADS * KM_BATCH), (int64_t)8192);
-    hipLaunchKernelGGL(k_keymap, dim3((unsigned)max(mb, (int64_t)1)), dim3(KM_THREADS), 0, stream,
-                       p);
-    // ids for the keys the lookup pass inserted
-    hipLaunchKernelGGL(k_compact, dim3(hb), dim3(CMP_THREADS), 0, stream, p);
+    if (ids) {
+        const int64_t mb =
+            min((p.m + KM_THREADS * KM_BATCH - 1) / (KM_THREADS * KM_BATCH), (int64_t)8192);
+        hipLaunchKernelGGL(k_keymap, dim3((unsigned)max(mb, (int64_t)1)), dim3(KM_THREADS), 0,
+                           stream, p);
+        // ids for the keys the lookup pass inserted
+        if (p.m > PREFIX_ALL)
+            hipLaunchKernelGGL(k_compact, dim3(hb), dim3(CMP_THREADS), 0, stream, p);
+    }
     // the distinct keys that can get a row are at most min(H + 1, cap + 1)
     // (more only on overflow, which is reported and ranked partially)
     const int64_t nmax = min((int64_t)p.H + 1, p.cap + 1);
@@ -1068,16 +1136,25 @@ hipError_t launch_key_map(const GroupParams& p, bool clear, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_aggregate(const GroupParams& p, hipStream_t stream)
+hipError_t launch_key_map(const GroupParams& p, bool clear, hipStream_t stream)
+{
+    return launch_keys(p, clear, true, stream);
+}
+
+static hipError_t launch_rows(const GroupParams& p, bool lookup, hipStream_t stream)
 {
     if (p.m <= 0) return p.n_keys_out ? launch_set_i64(p.n_keys_out, 0, stream) : hipSuccess;
     const unsigned ranges = (unsigned)((p.cap + AGG_IDS - 1) / AGG_IDS);
     const unsigned kb = (unsigned)max((int64_t)1, (p.cap + FIN_KEYS - 1) / FIN_KEYS);
     if (ranges > 0 && p.chunk <= (int64_t)AGG_THREADS * AGG_BATCH) {
-        hipLaunchKernelGGL(k_agg_one, dim3((unsigned)p.nchunks, ranges), dim3(AGG_THREADS), 0,
-                           stream, p);
+        if (lookup)
+            hipLaunchKernelGGL(k_agg_one<true>, dim3((unsigned)p.nchunks, ranges), dim3(AGG_THREADS),
+                               0, stream, p);
+        else
+            hipLaunchKernelGGL(k_agg_one<false>, dim3((unsigned)p.nchunks, ranges),
+                               dim3(AGG_THREADS), 0, stream, p);
         const unsigned kb1 = (unsigned)max((int64_t)1, (p.cap + FO_KEYS - 1) / FO_KEYS);
-        hipLaunchKernelGGL(k_fin_one, dim3(kb1), dim3(FO_KEYS * FO_GROUPS), 0, stream, p);
+        hipLaunchKernelGGL(k_fin_one, dim3(kb1), dim3(FO_THREADS), 0, stream, p);
     } else if (ranges > 0) {
         const unsigned ranges_sum = (unsigned)((p.cap + SUM_IDS - 1) / SUM_IDS);
         hipLaunchKernelGGL(k_agg_sum, dim3((unsigned)p.nchunks, ranges_sum), dim3(AGG_THREADS), 0,
@@ -1093,6 +1170,11 @@ hipError_t launch_aggregate(const GroupParams& p, hipStream_t stream)
     return hipGetLastError();
 }
 
+hipError_t launch_aggregate(const GroupParams& p, hipStream_t stream)
+{
+    return launch_rows(p, false, stream);
+}
+
 hipError_t launch_groupby(const GroupParams& p, hipStream_t stream)
 {
     if (p.m <= 0) return p.n_keys_out ? launch_set_i64(p.n_keys_out, 0, stream) : hipSuccess;
@@ -1100,9 +1182,12 @@ hipError_t launch_groupby(const GroupParams& p, hipStream_t stream)
         hipLaunchKernelGGL(k_group_small, dim3(1), dim3(GS_THREADS), 0, stream, p);
         return hipGetLastError();
     }
-    const hipError_t e = launch_key_map(p, false, stream);
+    // few enough intervals that every key is inserted at once: the aggregation
+    // looks the ids up itself (two or three launches fewer)
+    const bool lookup = p.m <= PREFIX_ALL && p.chunk <= (int64_t)AGG_THREADS * AGG_PER_LOOKUP;
+    const hipError_t e = launch_keys(p, false, !lookup, stream);
     if (e != hipSuccess) return e;
-    return launch_aggregate(p, stream);
+    return launch_rows(p, lookup, stream);
 }
 
 }  // namespace mag

@@ -172,7 +172,10 @@ def test_degenerate_cases():
 # capacity equal to the key count
 @pytest.mark.parametrize("m,keys", [(1, 1), (2, 2), (63, 1), (64, 64), (255, 255), (256, 256),
                                     (257, 257), (1000, 300), (2049, 513), (4095, 4095),
-                                    (4096, 4096), (4096, 2), (4097, 4097), (5000, 70)])
+                                    (4096, 4096), (4096, 2), (4097, 4097), (5000, 70),
+                                    # the aggregation's own lookups (up to 262,144)
+                                    (8193, 8193), (100_000, 416), (262_144, 20_000),
+                                    (262_145, 20_000)])
 def test_small_groupings(m, keys):
     rng = np.random.default_rng(m * 7 + keys)
     n = 3 * m + 50
