@@ -209,16 +209,16 @@ struct TimerSlot {
     const void* ws = nullptr;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     bool pending = false;          // events recorded by an asynchronous call, not read yet
-    bool status_pending = false;   // an asynchronous call copied its status here
+    bool status_pending = false;   // an asynchronous call sends its status here
     hipStream_t stream = nullptr;  // the stream that call was enqueued on
-    // recorded right after that call's status copy: finishing waits for this
+    // recorded right after that call's last kernel: finishing waits for this
     // call alone, not for later work on its stream (the next call of a
     // caller that keeps several in flight)
     hipEvent_t done = nullptr;
     // a call with a group stream: recorded after its trace integration, waited
     // for by the group stream
     hipEvent_t split = nullptr;
-    mag::Status* host_status = nullptr;  // pinned host copy of the status block
+    mag::Status* host_status = nullptr;  // pinned host copies of the status block(s)
     // an asynchronous mag_diff on this workspace: what its conclusion needs
     // besides the status block (table sizes or bounds, rows asked for, whether
     // a size is read on the device)
@@ -228,6 +228,9 @@ struct TimerSlot {
     bool busy() const { return pending || status_pending; }
 };
 constexpr size_t TIMER_KEEP = 16;
+// status blocks in a record's buffer: a batch of up to this many comparisons
+// sends them all there
+constexpr int HOST_STATUS = 16;
 constexpr size_t TIMER_MAX = 4096;
 thread_local std::vector<std::unique_ptr<TimerSlot>> g_timers;
 thread_local uint64_t g_timer_clock = 0;
@@ -269,7 +272,9 @@ TimerSlot* timer_slot(const void* ws, bool create)
         }
     if (!t->host_status) {
         void* h = nullptr;
-        if (hipHostMalloc(&h, sizeof(mag::Status), hipHostMallocDefault) != hipSuccess)
+        // (portable: a kernel of whichever GPU the workspace is on writes it)
+        if (hipHostMalloc(&h, HOST_STATUS * sizeof(mag::Status),
+                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
             return nullptr;
         t->host_status = static_cast<mag::Status*>(h);
     }
@@ -433,13 +438,28 @@ int interpret_status(const mag::Status& st, mag_key_stats* per_key, mag_summary*
     return MAG_OK;
 }
 
-// copy a device status block to the host (through the workspace's pinned
-// buffer) and synchronize `stream`
-int read_status(const mag::Status* status, hipStream_t stream, mag::Status* out)
+// the pinned buffer that the last kernel of a call on this workspace sends the
+// status block to, or NULL: then the block is copied after the call instead
+mag::Status* status_target(const void* workspace)
 {
-    TimerSlot* t = timer_slot(status, true);
-    mag::Status* dst = (t && t->host_status) ? t->host_status : out;
+    TimerSlot* t = timer_slot(workspace, true);
+    return t ? t->host_status : nullptr;
+}
+
+// a device status block on the host, `stream` synchronized: `sent` is where
+// the call's last kernel wrote it (NULL: copied now, through the workspace's
+// pinned buffer)
+int read_status(const mag::Status* status, const mag::Status* sent, hipStream_t stream,
+                mag::Status* out)
+{
     hipError_t e2;
+    if (sent) {
+        if ((e2 = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e2, "synchronize");
+        *out = *sent;
+        return MAG_OK;
+    }
+    mag::Status* t = status_target(status);
+    mag::Status* dst = t ? t : out;
     if ((e2 = hipMemcpyAsync(dst, status, sizeof(mag::Status), hipMemcpyDeviceToHost, stream)) !=
         hipSuccess)
         return hip_fail(e2, "status copy");
@@ -448,29 +468,27 @@ int read_status(const mag::Status* status, hipStream_t stream, mag::Status* out)
     return MAG_OK;
 }
 
-int finish_status(const mag::Status* status, mag_key_stats* per_key, mag_summary* summary,
-                  hipStream_t stream)
+int finish_status(const mag::Status* status, const mag::Status* sent, mag_key_stats* per_key,
+                  mag_summary* summary, hipStream_t stream)
 {
     mag::Status st;
-    const int rc = read_status(status, stream, &st);
+    const int rc = read_status(status, sent, stream, &st);
     if (rc != MAG_OK) return rc;
     return interpret_status(st, per_key, summary);
 }
 
-// the end of an asynchronous call: its status block is copied to the pinned
-// buffer of the workspace's record on `stream`, and the record keeps that
-// stream (and the timing events, when timed) for mag_attribute_finish.
+// the end of an asynchronous call: its last kernel sends the status block to
+// the pinned buffer of the workspace's record (`sent`), and the record keeps
+// the stream (and the timing events, when timed) for mag_attribute_finish.
 // Without a record, finishing reads the status block from the device.
-int async_status(const void* workspace, const mag::Status* status, hipStream_t stream, bool timed)
+int async_status(const void* workspace, const mag::Status* sent, hipStream_t stream, bool timed)
 {
-    TimerSlot* t = timer_slot(workspace, true);
+    TimerSlot* t = sent ? timer_slot(workspace, true) : nullptr;
     if (!t) return MAG_OK;
     t->pending = timed;
     t->stream = stream;
-    if (t->host_status) {
-        hipError_t e = hipMemcpyAsync(t->host_status, status, sizeof(mag::Status),
-                                      hipMemcpyDeviceToHost, stream);
-        if (e != hipSuccess) return hip_fail(e, "status copy");
+    if (t->host_status == sent) {
+        hipError_t e;
         if ((e = hipEventRecord(t->done, stream)) != hipSuccess) return hip_fail(e, "event record");
         t->status_pending = true;
     }
@@ -491,6 +509,7 @@ struct Job {
     int64_t* start_idx = nullptr;
     int64_t* end_idx = nullptr;
     hipStream_t stream = nullptr;
+    mag::Status* host = nullptr;  // status_target, where the last kernel sends the status block
 
     bool validate() const { return (flags & MAG_SKIP_VALIDATE) == 0; }
 
@@ -566,7 +585,7 @@ struct Job {
     {
         if (pl.m == 0 || !per_key) {
             // no aggregation: one workgroup adds up the energies and the fold
-            const hipError_t e2 = mag::launch_energy_total(energy, pl.m, w.fold, w.status, stream);
+            const hipError_t e2 = mag::launch_energy_total(energy, pl.m, w.fold, w.status, host, stream);
             if (e2 != hipSuccess || pl.m > 0) return e2;
             return (per_key && per_key->n_keys_device)
                        ? mag::launch_set_i64(per_key->n_keys_device, 0, stream)
@@ -597,6 +616,7 @@ struct Job {
         gp.ctot = w.ctot;
         gp.fold = w.fold;  // NULL in the counter mode: its fold kernel sets those totals
         gp.n_keys_out = per_key->n_keys_device;
+        gp.host = host;
         if (pl.lat) {
             gp.s = s;
             gp.e = e;
@@ -615,7 +635,7 @@ struct Job {
     // read the status block back and turn it into the call's result
     int conclude(mag_key_stats* per_key, mag_summary* summary)
     {
-        return finish_status(w.status, per_key, summary, stream);
+        return finish_status(w.status, host, per_key, summary, stream);
     }
 };
 
@@ -753,6 +773,7 @@ int attribute_impl(const double* timestamps, const float* power, int64_t n_sampl
     // timing (MAG_TIME_KERNELS): events 1 and 2 travel with the tile kernel's
     // dispatch, event 3 follows the call's last kernel
     EventTimer timer(!no_alloc && (job.flags & MAG_TIME_KERNELS) != 0, stream, workspace);
+    if (!no_alloc) job.host = status_target(workspace);
     if ((e = mag::launch_init(job.w.status, job.w.cnt_fin, (int64_t)job.pl.S * (NT + 1),
                               timestamps, n_samples, stream)) != hipSuccess)
         return hip_fail(e, "init");
@@ -794,10 +815,10 @@ int attribute_impl(const double* timestamps, const float* power, int64_t n_sampl
         return rc;
     }
     if (job.flags & MAG_ASYNC)
-        // results, errors and timings come from mag_attribute_finish; the status
-        // block is copied to pinned host memory now, so that finishing needs
-        // no further device work
-        return async_status(workspace, job.w.status, stream, timer.on);
+        // results, errors and timings come from mag_attribute_finish; the last
+        // kernel sends the status block to pinned host memory, so that finishing
+        // needs no further device work
+        return async_status(workspace, job.host, stream, timer.on);
     rc = job.conclude(per_key, summary);
     if (summary) {
         summary->tile_kernel_ms = timer.ms(1, 2);
@@ -1021,6 +1042,7 @@ int mag_attribute_counter(const double* timestamps, const double* counter, int64
 
     hipError_t e;
     EventTimer timer((flags & MAG_TIME_KERNELS) != 0, stream, workspace);
+    job.host = status_target(workspace);
     if ((e = mag::launch_init_status(job.w.status, nullptr, 0, stream)) != hipSuccess)
         return hip_fail(e, "init");
     if ((e = mag::launch_counter(cp, stream, timer.on ? timer.slot->ev[1] : nullptr,
@@ -1029,7 +1051,7 @@ int mag_attribute_counter(const double* timestamps, const double* counter, int64
     if ((e = mag::launch_counter_fold(cp, stream)) != hipSuccess) return hip_fail(e, "fold kernel");
     if ((e = job.grouping(keys_out, per_key)) != hipSuccess) return hip_fail(e, "group-by");
     timer.mark(3);
-    if (flags & MAG_ASYNC) return async_status(workspace, job.w.status, stream, timer.on);
+    if (flags & MAG_ASYNC) return async_status(workspace, job.host, stream, timer.on);
     rc = job.conclude(per_key, summary);
     if (summary) {
         summary->tile_kernel_ms = timer.ms(1, 2);
@@ -1048,9 +1070,9 @@ int mag_attribute_finish(const void* workspace, mag_key_stats* per_key, mag_summ
     TimerSlot* t = timer_slot(workspace, false);
     int rc;
     if (t && t->status_pending && t->host_status) {
-        // the call already copied its status to pinned memory on its own
-        // stream (which may differ from `stream`) and recorded an event
-        // after the copy: that event is waited for, not later work
+        // the call's last kernel sends its status to pinned memory on its own
+        // stream (which may differ from `stream`) and an event follows it:
+        // that event is waited for, not later work
         t->status_pending = false;
         hipError_t e2;
         if ((e2 = hipEventSynchronize(t->done)) != hipSuccess) {
@@ -1059,7 +1081,8 @@ int mag_attribute_finish(const void* workspace, mag_key_stats* per_key, mag_summ
         }
         rc = interpret_status(*t->host_status, per_key, summary);
     } else {
-        rc = finish_status(static_cast<const mag::Status*>(workspace), per_key, summary, stream);
+        rc = finish_status(static_cast<const mag::Status*>(workspace), nullptr, per_key, summary,
+                           stream);
         t = timer_slot(workspace, false);
     }
     if (summary) {
@@ -1428,6 +1451,7 @@ int mag_stream_end(mag_stream* h, uint64_t* keys_out, mag_key_stats* per_key, ma
     int rc = MAG_OK;
     hipError_t e;
     const int64_t n = h->received;
+    job.host = status_target(job.w.status);
     const int64_t NT = (n - 1 + mag::TILE - 1) / mag::TILE;
     if (h->failed) {
         rc = fail(MAG_E_STATE, "a previous call on this stream failed");
@@ -1649,6 +1673,7 @@ int enqueue_diff(const uint64_t* keysA, const mag_key_stats* statsA, const uint6
     c.base = static_cast<char*>(workspace);
     p.status = c.take<mag::Status>(1);
     carve_candidates(c, p.na, k, &p);
+    p.host = status_target(workspace);
     hipError_t e;
     // every field of the status block the call reads is written by its kernels
     if ((e = mag::launch_diff(p, stream)) != hipSuccess) return hip_fail(e, "diff kernels");
@@ -1663,7 +1688,7 @@ int run_diff(const uint64_t* keysA, const mag_key_stats* statsA, const uint64_t*
     int rc = enqueue_diff(keysA, statsA, keysB, statsB, k, out, p, workspace, workspace_bytes,
                           stream);
     if (rc != MAG_OK) return rc;
-    rc = read_status(p.status, stream, st);
+    rc = read_status(p.status, p.host, stream, st);
     if (rc != MAG_OK) return rc;
     return conclude_diff(p, *st, out);
 }
@@ -1700,14 +1725,12 @@ int mag_diff_async(const uint64_t* keysA, const mag_key_stats* statsA, const uin
     int rc = enqueue_diff(keysA, statsA, keysB, statsB, k, out, p, workspace, workspace_bytes,
                           stream);
     if (rc != MAG_OK) return rc;
-    // the status block (first in the workspace) goes to the pinned buffer of
-    // the workspace's record, in stream order
+    // the last kernel sends the status block to the pinned buffer of the
+    // workspace's record
     TimerSlot* t = timer_slot(workspace, true);
-    if (!t || !t->host_status)
+    if (!t || !t->host_status || t->host_status != p.host)
         return fail(MAG_E_HIP, "no host buffer for the status of an asynchronous call");
-    hipError_t e =
-        hipMemcpyAsync(t->host_status, p.status, sizeof(mag::Status), hipMemcpyDeviceToHost, stream);
-    if (e != hipSuccess) return hip_fail(e, "status copy");
+    hipError_t e;
     if ((e = hipEventRecord(t->done, stream)) != hipSuccess) return hip_fail(e, "event record");
     t->status_pending = true;
     t->stream = stream;
@@ -1767,18 +1790,22 @@ int mag_diff_batch(const uint64_t* keysA, const mag_key_stats* statsA, int32_t n
     Carver c;
     c.base = static_cast<char*>(workspace);
     mag::Status* status = c.take<mag::Status>((size_t)n_candidates);
+    TimerSlot* t = n_candidates <= HOST_STATUS ? timer_slot(workspace, true) : nullptr;
+    mag::Status* sent = (t && !t->busy()) ? t->host_status : nullptr;
     for (int32_t i = 0; i < n_candidates; ++i) {
         ps[i].status = status + i;
+        ps[i].host = sent ? sent + i : nullptr;
         carve_candidates(c, na, k, &ps[i]);
     }
     hipError_t e;
     if ((e = mag::launch_diff_batch(ps.data(), n_candidates, stream)) != hipSuccess)
         return hip_fail(e, "diff kernels");
     std::vector<mag::Status> st((size_t)n_candidates);
-    if ((e = hipMemcpyAsync(st.data(), status, sizeof(mag::Status) * (size_t)n_candidates,
-                            hipMemcpyDeviceToHost, stream)) != hipSuccess)
+    if (!sent && (e = hipMemcpyAsync(st.data(), status, sizeof(mag::Status) * (size_t)n_candidates,
+                                     hipMemcpyDeviceToHost, stream)) != hipSuccess)
         return hip_fail(e, "status copy");
     if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "synchronize");
+    if (sent) std::copy(sent, sent + n_candidates, st.begin());
     for (int32_t i = 0; i < n_candidates; ++i) {
         const int rc = conclude_diff(ps[i], st[i], &out[i]);
         if (rc != MAG_OK) return rc;

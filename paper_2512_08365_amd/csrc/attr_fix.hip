@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void k_init(Status* st, int64_t* cnt_fin, int6
 }
 
 __global__ __launch_bounds__(1024) void k_energy_total(const double* energy, int64_t m,
-                                                      const double2* fold, Status* st)
+                                                      const double2* fold, Status* st, Status* host)
 {
     __shared__ double red[16];
     __shared__ double2 redf[16];
@@ -274,6 +274,7 @@ __global__ __launch_bounds__(1024) void k_energy_total(const double* energy, int
             st->trace_energy = t.x;
             st->idle_energy = t.y;
         }
+        send_status(st, host);
     }
 }
 
@@ -329,9 +330,9 @@ hipError_t launch_fix(const FixParams& p, hipStream_t stream)
 }
 
 hipError_t launch_energy_total(const double* energy, int64_t m, const double2* fold, Status* st,
-                               hipStream_t stream)
+                               Status* host, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_energy_total, dim3(1), dim3(1024), 0, stream, energy, m, fold, st);
+    hipLaunchKernelGGL(k_energy_total, dim3(1), dim3(1024), 0, stream, energy, m, fold, st, host);
     return hipGetLastError();
 }
 

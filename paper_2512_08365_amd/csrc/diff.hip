@@ -306,6 +306,7 @@ __global__ __launch_bounds__(JOIN_ROWS) void k_diff_write(const A a)
             p.status->n_flag = s_[2];
             p.status->n_waste = s_[3];
             p.status->err = s_[4];
+            send_status(p.status, p.host);
         }
     }
     const int i = threadIdx.x;

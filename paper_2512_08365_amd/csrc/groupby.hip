@@ -549,6 +549,8 @@ __global__ __launch_bounds__(FIN_KEYS * FIN_GROUPS) void k_fin_m2(const GroupPar
     __shared__ double qd[FIN_GROUPS][FIN_KEYS];
     const int kl = threadIdx.x % FIN_KEYS, grp = threadIdx.x / FIN_KEYS;
     const int64_t id = (int64_t)blockIdx.x * FIN_KEYS + kl;
+    // (k_fin_sum, before this kernel, has set the block's last fields)
+    if (blockIdx.x == 0 && threadIdx.x == 0) send_status(p.status, p.host);
     // loads requested before the key count is read, as in k_fin_sum
     double m2 = 0.0, du = 0.0;
     if (id < p.cap)
@@ -838,10 +840,13 @@ __global__ __launch_bounds__(FO_THREADS) void k_fin_one(const GroupParams p)
     }
     if (blockIdx.x == 0) {
         write_totals(p, red, FO_THREADS);
-        if (p.kstat != p.status && threadIdx.x == 0) {
-            // a key plan built beforehand: its counts become the call's
-            p.status->n_unique = p.kstat->n_unique;
-            if (p.kstat->overflow) p.status->overflow = 1u;
+        if (threadIdx.x == 0) {
+            if (p.kstat != p.status) {
+                // a key plan built beforehand: its counts become the call's
+                p.status->n_unique = p.kstat->n_unique;
+                if (p.kstat->overflow) p.status->overflow = 1u;
+            }
+            send_status(p.status, p.host);
         }
     }
 }
@@ -1076,6 +1081,7 @@ __global__ __launch_bounds__(GS_THREADS) void k_group_small(const GroupParams p)
             p.status->idle_energy = idle;
         }
         if (p.n_keys_out) *p.n_keys_out = nk;
+        send_status(p.status, p.host);
     }
 }
 

@@ -161,6 +161,7 @@ struct GroupParams {
     // elsewhere)
     double* ctot;         // [nchunks]
     const double2* fold;  // [FOLD_BLOCKS] or NULL
+    Status* host;         // the status block in pinned host memory, or NULL (send_status)
 };
 
 // per-operator energy from a delayed cumulative energy counter
@@ -230,6 +231,7 @@ struct DiffParams {
     double* out_la;
     double* out_lb;
     int32_t* out_verdict;
+    Status* host;         // the status block in pinned host memory, or NULL (send_status)
 };
 
 // Workgroup barrier for LDS traffic only: waits for this wave's LDS operations
@@ -240,6 +242,26 @@ struct DiffParams {
 __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The status block, written to the call's pinned host buffer by the thread that
+// sets its last fields, in the call's last kernel.  A copy enqueued after that
+// kernel costs a launch of its own (a 4 us copy kernel and the 5 us gap before
+// it); these stores ride with the kernel's end.  dst NULL: nothing is written.
+__device__ __forceinline__ void send_status(const Status* src, Status* dst)
+{
+    if (!dst) return;
+    static_assert(sizeof(Status) % 8 == 0 && alignof(Status) == 8, "copied in 8-byte words");
+    uint64_t w[sizeof(Status) / 8];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(Status) / 8); ++i)
+        w[i] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(src) + i, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(Status) / 8); ++i)
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(dst) + i, w[i], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
 }
 
 // launchers (return hipError_t of the launch)
@@ -402,6 +424,7 @@ hipError_t launch_counter_fold(const CounterParams& p, hipStream_t stream);
 // attributed energy = sum of energy[m]; trace and idle energy from the fold
 // partials (fold NULL: left alone)
 hipError_t launch_energy_total(const double* energy, int64_t m, const double2* fold, Status* st,
+                               Status* host,
                                hipStream_t stream);
 hipError_t launch_diff(const DiffParams& p, hipStream_t stream);
 // comparisons per launch of a batch (their parameters travel as kernel arguments)

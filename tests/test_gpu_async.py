@@ -170,3 +170,22 @@ def test_asynchronous_diffs_match_synchronous_ones():
 def ctypes_ptr(t):
     import ctypes
     return ctypes.c_void_p(t.data_ptr())
+
+
+@pytest.mark.parametrize("n", [1, 16, 17])
+def test_batched_comparisons_deliver_every_status(n):
+    """Batches around the number of status blocks a record's host buffer holds
+    (16): every candidate's rows and counts are those of its own comparison."""
+    import torch
+    import paper_2512_08365_amd as mag
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    tabs = []
+    for i in range(4):
+        c = synth.tiny_case(2300 + i, n=6000, streams=2, per_stream=80)
+        c["key"] = (c["key"] % np.uint64(9 + 4 * i)).astype(np.uint64)
+        tabs.append(_run(mag, to_gpu(c), c)[1])
+    want = [mag.diff(tabs[0], b, 7) for b in tabs]
+    log(f"[async] batch of {n}")
+    for i, got in enumerate(mag.diff_batch(tabs[0], [tabs[j % 4] for j in range(n)], 7)):
+        _same_rank(got, want[i % 4], f"candidate {i}")
