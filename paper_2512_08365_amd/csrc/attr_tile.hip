@@ -966,6 +966,23 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
 
     SampleRegs sr;
     if (vector_tile(b0)) sample_prefetch(sr, b0, lane);
+    // Outputs are written one round late, once the next round's window has
+    // arrived, and their arrays are held in scalar registers, so that choosing
+    // one per lane is a register select.  Written at once, through a per-lane
+    // load of the argument chosen, every round waited for the window and the
+    // samples it had just requested.  Null: nothing pending.
+    const gptr<double> g_energy = sreg(p.energy), g_head = sreg(p.head), g_tail = sreg(p.tail);
+    const gptr<int64_t> g_start = sreg(p.start_idx), g_end = sreg(p.end_idx);
+    gptr<int64_t> pend_idx = nullptr;  // the lane's endpoint index
+    int64_t pend_idx_v = 0;
+    gptr<double> pend_en = nullptr;    // an interval's energy, or a piece of it
+    double pend_en_v = 0.0;
+    auto flush = [&]() {
+        if (pend_idx) *pend_idx = pend_idx_v;
+        if (pend_en) *pend_en = pend_en_v;
+        pend_idx = nullptr;
+        pend_en = nullptr;
+    };
     unsigned err = 0u;
     double idle = 0.0;    // this lane's share of the idle energy
     double w_wave = 0.0;  // the run's trace energy (uniform)
@@ -978,7 +995,6 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
         float pT;
         const double FT = sample_stage(sr, b, L, lane, sm.tF, sm.P, err, tT, pT);
         w_wave += FT;
-        if (lane == 0) kk->cnt[b] = sq;
         // the interval open at the tile's start began in an earlier tile
         int started = 0;
         wave_sync();
@@ -1014,6 +1030,8 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
             const int lead = (inm == ~0ull) ? WAVE : (int)__builtin_ctzll(~inm);
             const bool fin = lead < WAVE;
             const int k = lead;
+            flush();  // the previous round's outputs, now that the window is here
+            if (first_round && lane == 0) kk->cnt[b] = sq;
             if (first_round && b + 1 < b1 && vector_tile(b + 1)) sample_prefetch(sr, b + 1, lane);
             first_round = false;
             const int64_t sqn = sq + k;
@@ -1058,8 +1076,9 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
             const double Fj = A0.y;  // prefix at the start of segment j (the tile's end: F_L)
             const int64_t gid = q >> 1;
             if (real) {
-                int64_t* idx = (q & 1) ? kk->end_idx : kk->start_idx;
-                if (idx) idx[gid] = j0 + j + 1;
+                const gptr<int64_t> idx = (q & 1) ? g_end : g_start;
+                pend_idx = idx ? idx + gid : nullptr;
+                pend_idx_v = j0 + j + 1;
             }
 
             // ---- the gap ending here, from the endpoint one lane below
@@ -1100,10 +1119,8 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
                 // an interval ending at this endpoint, or open at the tile's
                 // end: complete when it began in this tile, else its piece here
                 const bool began = (lane > 0) || started;
-                if (real)
-                    *(began ? &kk->energy[gid] : &kk->head[b]) = Q;
-                else
-                    *(began ? &kk->tail[b] : &kk->head[b]) = Q;
+                pend_en = !began ? g_head + b : real ? g_energy + gid : g_tail + b;
+                pend_en_v = Q;
             }
             // ---- commit (uniform)
             if (k > 0) {
@@ -1122,6 +1139,7 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
         wave_sync();
     }
 
+    flush();
     // the run's trace and idle energy, at its first tile (k_fix adds them up)
     const double It = wave_sum(idle);
     const KArgs k = kargs();
