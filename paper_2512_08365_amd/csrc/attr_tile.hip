@@ -106,6 +106,15 @@ __device__ __forceinline__ double recip(double d)
     return (d > 0.0) ? r : INFINITY;
 }
 
+// truncation that saturates (not a number: zero), as the instruction does; a C++
+// conversion leaves values outside the integer's range undefined
+__device__ __forceinline__ int cvt_i32(double v)
+{
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 // the value of a window entry past the end of its stream
 __device__ const double kPastEnd = INFINITY;
 
@@ -304,6 +313,13 @@ __device__ __forceinline__ void sample_prefetch(SampleRegs& r, int b, int lane)
     r.ppl = k->P[g + C];
 }
 
+// a power sample that is negative or not finite (-0 passes), in one comparison
+__device__ __forceinline__ bool bad_power(float v)
+{
+    // class bits: NaN 0-1, -inf 2, negative normal 3, negative denormal 4, +inf 9
+    return __builtin_amdgcn_classf(v, 0x21f);
+}
+
 // checks, segment energies S_j = (P_j + P_{j+1}) (t_{j+1} - t_j) / 2 and the
 // tile-local prefix F (a per-lane running sum plus a DPP scan of the lane
 // totals) of tile b (L segments), staged in LDS as {t, F} and P; returns the
@@ -370,7 +386,7 @@ __device__ __forceinline__ double sample_stage(const SampleRegs& r, int b, int L
         }
         uint64_t pbad = 0;
 #pragma unroll
-        for (int u = 0; u <= C; ++u) pbad |= __ballot(!((pv[u] >= 0.0f) & (pv[u] < INFINITY)));
+        for (int u = 0; u <= C; ++u) pbad |= __ballot(bad_power(pv[u]));
         err |= (tbad ? ERR_TIMESTAMPS : 0u) | (pbad ? ERR_POWER : 0u);
     }
     double f[C + 1];
@@ -636,19 +652,18 @@ __global__ __launch_bounds__(WAVE) void k_tile(const TileParams p)
             const double xp = (my_r > 0) ? sm.wx[(my_a << LW) + max(my_r - 1, 0)] : lx_a;
 
             // ---- segment j: t_j < x <= t_{j+1}; sample index j0 + j + 1
+            // (the guess or a neighbour of it, checked with the segment's own ends)
             int j;
             {
-                const int jg = (int)fmin(fmax((x - t_begin) * inv_dt, 0.0), (double)(L - 1));
-                const int c0 = max(0, min(jg - 1, L - 3));
-                const double u0 = t_at(c0), u1 = t_at(min(c0 + 1, L)), u2 = t_at(min(c0 + 2, L)),
-                             u3 = t_at(min(c0 + 3, L));
-                j = (u0 < x && x <= u1) ? c0
-                  : (c0 + 1 < L && u1 < x && x <= u2) ? c0 + 1
-                  : (c0 + 2 < L && u2 < x && x <= u3) ? c0 + 2 : -1;
+                const int jg = max(min(cvt_i32((x - t_begin) * inv_dt), L - 2), 0);
+                const double u1 = t_at(jg), u2 = t_at(jg + 1);
+                j = max(min(jg + (x > u2 ? 1 : 0) - (x <= u1 ? 1 : 0), L - 1), 0);
                 if (!real) j = L;
             }
-            if (__ballot(j < 0) != 0ull) {
-                if (j < 0) {
+            double2 A0 = tF_at(j), A1 = tF_at(min(j + 1, L));
+            const bool miss = real && !(A0.x < x && x <= A1.x);
+            if (__ballot(miss) != 0ull) {
+                if (miss) {
                     // first sample index >= x (x > t_0 of the tile for sorted input)
                     int lo = 0, hi = L;
                     while (lo < hi) {
@@ -656,9 +671,10 @@ __global__ __launch_bounds__(WAVE) void k_tile(const TileParams p)
                         if (t_at(mid) < x) lo = mid + 1; else hi = mid;
                     }
                     j = min(max(lo, 1), L) - 1;
+                    A0 = tF_at(j);
+                    A1 = tF_at(j + 1);
                 }
             }
-            const double2 A0 = tF_at(j), A1 = tF_at(min(j + 1, L));
             const double pj = P_at(j), pj1 = P_at(min(j + 1, L));
             // interpolated power and the pieces of segment j left and right of x
             const double rh = recip(A1.x - A0.x);
@@ -910,6 +926,12 @@ __global__ __launch_bounds__(WAVE) void k_tile(const TileParams p)
 // piece of an interval still open there.  Same outputs as k_tile: energies,
 // sample indices, head/tail pieces, per-tile cursors, per-run trace and idle
 // energies.
+// 360M samples with 50M intervals, in twelve launches (floor: 5.5 GB, 0.89 ms):
+// 2.04 ms with outputs stored where they arise, 1.80 ms stored a round late
+// (the loop below), 1.75 ms with two samples read for the segment search in
+// place of four and no test for the tile's last sample there.  Now bound by the
+// vector units' instruction issue (60 % busy at four waves each) and the LDS
+// round trips of the search between them.
 // ---------------------------------------------------------------------------
 struct SeqLds {
     // local samples 0 .. T - 1 ({t, F} and P at [i % C][i / C]); a whole
@@ -954,12 +976,18 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
 
     // window: lane l holds endpoint sq + l; past the stream's end it reads +inf
     // from device memory, so the value needs no select after its load
+    // (lane l's byte offset from the window's first interval, by the parity of
+    // the window's first endpoint: two sums where the endpoint's own index would
+    // be taken apart)
     const int64_t e_minus_s = (int64_t)((const char*)p.e - (const char*)p.s);
+    const int64_t w_even = 8 * (int64_t)(lane >> 1) + ((lane & 1) ? e_minus_s : 0);
+    const int64_t w_odd = 8 * (int64_t)((lane + 1) >> 1) + ((lane & 1) ? 0 : e_minus_s);
     auto wload = [&](int64_t cur) -> double {
-        const int64_t q = cur + lane;
-        const gptr<const double> ptr = (q < len)
-            ? (gptr<const double>)endpoint_addr((uint64_t)p.s, e_minus_s, q)
-            : (gptr<const double>)&kPastEnd;
+        const int left = (int)min(len - cur, (int64_t)WAVE);
+        const uint64_t at = (uint64_t)p.s + 8 * (uint64_t)(cur >> 1) +
+                            (uint64_t)((cur & 1) ? w_odd : w_even);
+        const gptr<const double> ptr =
+            (lane < left) ? (gptr<const double>)at : (gptr<const double>)&kPastEnd;
         return *ptr;
     };
     double ew = wload(sq);
@@ -973,6 +1001,7 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
     // samples it had just requested.  Null: nothing pending.
     const gptr<double> g_energy = sreg(p.energy), g_head = sreg(p.head), g_tail = sreg(p.tail);
     const gptr<int64_t> g_start = sreg(p.start_idx), g_end = sreg(p.end_idx);
+    const bool has_idx = g_start || g_end;
     gptr<int64_t> pend_idx = nullptr;  // the lane's endpoint index
     int64_t pend_idx_v = 0;
     gptr<double> pend_en = nullptr;    // an interval's energy, or a piece of it
@@ -998,22 +1027,18 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
         // the interval open at the tile's start began in an earlier tile
         int started = 0;
         wave_sync();
-        // local sample i <= L (i = T only for a whole tile; its column index
-        // is wrapped so that the LDS read stays inside the arrays)
-        auto tF_at = [&](int i) -> double2 {
-            const double2 v = sm.tF[i & (C - 1)][(i >> 3) & (WAVE - 1)];
-            return (i == T) ? make_double2(tT, FT) : v;
-        };
-        auto t_at = [&](int i) -> double {
-            const double v = sm.tF[i & (C - 1)][(i >> 3) & (WAVE - 1)].x;
-            return (i == T) ? tT : v;
-        };
-        auto P_at = [&](int i) -> double {
-            const float v = sm.P[i & (C - 1)][(i >> 3) & (WAVE - 1)];
-            return (double)((i == T) ? pT : v);
-        };
+        // local sample i < T; the tile's last sample, local index L, apart (a
+        // whole tile's is in uniform registers)
+        auto tF_at = [&](int i) -> double2 { return sm.tF[i & (C - 1)][i >> 3]; };
+        auto t_at = [&](int i) -> double { return sm.tF[i & (C - 1)][i >> 3].x; };
+        auto P_at = [&](int i) -> double { return (double)sm.P[i & (C - 1)][i >> 3]; };
+        double tau_end = tT, FL = FT;
+        if (L < T) {
+            const double2 v = tF_at(L);
+            tau_end = v.x;
+            FL = v.y;
+        }
         const double t_begin = t_at(0);
-        const double tau_end = t_at(L);
         const double inv_dt = (double)L * recip(tau_end - t_begin);
         // where the round starts (uniform): the tile's first sample, later the
         // previous round's last endpoint -- x, its interpolated power, the
@@ -1039,47 +1064,62 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
 
             const bool real = lane < k;
             const bool tail_lane = fin && lane == k;
-            const int64_t q = sq + lane;  // the tail lane: sqn
+            // the lane's endpoint is sq + lane (the tail lane's: sqn), of interval gi + gl
+            const int64_t gi = sq >> 1;
+            const uint32_t gl = (uint32_t)(lane + (int)(sq & 1)) >> 1;
+            const bool open = ((lane + (int)(sq & 1)) & 1) != 0;  // it is an end: the gap before
+                                                                  // it lies inside an interval
             const double x = real ? xw : tau_end;
             // an entry that is neither inside the tile nor after its end is
             // not a number
-            if (tail_lane && kk->validate && q < len && !(xw > tau_end)) err |= ERR_INTERVAL;
+            if (tail_lane && kk->validate && sqn < len && !(xw > tau_end)) err |= ERR_INTERVAL;
 
             // ---- segment j: t_j < x <= t_{j+1}; sample index j0 + j + 1
+            // (the guess or a neighbour of it, checked with the segment's own
+            // ends; a lane without an endpoint takes the tile's last segment)
             int j;
             {
-                const int jg = (int)fmin(fmax((x - t_begin) * inv_dt, 0.0), (double)(L - 1));
-                const int c0 = max(0, min(jg - 1, L - 3));
-                const double u0 = t_at(c0), u1 = t_at(min(c0 + 1, L)), u2 = t_at(min(c0 + 2, L)),
-                             u3 = t_at(min(c0 + 3, L));
-                j = (u0 < x && x <= u1) ? c0
-                  : (c0 + 1 < L && u1 < x && x <= u2) ? c0 + 1
-                  : (c0 + 2 < L && u2 < x && x <= u3) ? c0 + 2 : -1;
-                if (!real) j = L;
+                const int jg = max(min(cvt_i32((x - t_begin) * inv_dt), L - 2), 0);
+                const double u1 = t_at(jg), u2 = t_at(jg + 1);
+                j = max(min(jg + (x > u2 ? 1 : 0) - (x <= u1 ? 1 : 0), L - 1), 0);
             }
-            if (__ballot(j < 0) != 0ull) {
-                if (j < 0) {
-                    int lo = 0, hi = L;
+            double2 A0, A1;
+            double pj, pj1;
+            auto segment = [&]() {
+                A0 = tF_at(j);
+                pj = P_at(j);
+                A1 = make_double2(tT, FT);
+                pj1 = (double)pT;
+                if (j + 1 < T) {
+                    A1 = tF_at(j + 1);
+                    pj1 = P_at(j + 1);
+                }
+            };
+            segment();
+            const bool miss = real && !(A0.x < x && x <= A1.x);
+            if (__ballot(miss) != 0ull) {
+                if (miss) {
+                    int lo = 0, hi = L;  // x <= tau_end: at most L - 1 is read
                     while (lo < hi) {
                         const int mid = (lo + hi) >> 1;
                         if (t_at(mid) < x) lo = mid + 1; else hi = mid;
                     }
                     j = min(max(lo, 1), L) - 1;
+                    segment();
                 }
             }
-            const double2 A0 = tF_at(j), A1 = tF_at(min(j + 1, L));
-            const double pj = P_at(j), pj1 = P_at(min(j + 1, L));
             const double rh = recip(A1.x - A0.x);
-            const double ph = !real ? pj : (x == A1.x) ? pj1 : pj + (pj1 - pj) * ((x - A0.x) * rh);
+            const double ph = (x == A1.x) ? pj1 : pj + (pj1 - pj) * ((x - A0.x) * rh);
             const double left = real ? ((pj + ph) * (x - A0.x)) * 0.5 : 0.0;
-            const double right = real ? ((ph + pj1) * (A1.x - x)) * 0.5 : 0.0;
-            const double Fj = A0.y;  // prefix at the start of segment j (the tile's end: F_L)
-            const int64_t gid = q >> 1;
-            if (real) {
-                const gptr<int64_t> idx = (q & 1) ? g_end : g_start;
-                pend_idx = idx ? idx + gid : nullptr;
+            const double right = ((ph + pj1) * (A1.x - x)) * 0.5;
+            // prefix at the start of segment j (the tile's end: F_L)
+            const double Fj = real ? A0.y : FL;
+            if (has_idx && real) {
+                const gptr<int64_t> idx = open ? g_end : g_start;
+                pend_idx = idx ? idx + gi + gl : nullptr;
                 pend_idx_v = j0 + j + 1;
             }
+            if (!real) j = L;
 
             // ---- the gap ending here, from the endpoint one lane below
             double px = dpp_f64<DPP_WAVE_SHR1, 0xf>(x);
@@ -1108,18 +1148,19 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
                     // the whole segments summed directly
                     double sum = 0.0;
                     for (int i = pjx + 1; i < j; ++i)
-                        sum += seg_energy(t_at(i), t_at(i + 1), (float)P_at(i), (float)P_at(i + 1));
+                        // (i + 1 <= j <= L, the tile's last sample where i + 1 = T)
+                        sum += seg_energy(t_at(i), i + 1 < T ? t_at(i + 1) : tT, (float)P_at(i),
+                                          i + 1 < T ? (float)P_at(i + 1) : pT);
                     whole = sum;
                 }
             }
             const double Q = same ? q_in : (pright + whole) + left;
-            const bool open = (q & 1) != 0;  // the gap lies inside an interval
             if (has_gap && !open) idle += Q;
             if (has_gap && open) {
                 // an interval ending at this endpoint, or open at the tile's
                 // end: complete when it began in this tile, else its piece here
                 const bool began = (lane > 0) || started;
-                pend_en = !began ? g_head + b : real ? g_energy + gid : g_tail + b;
+                pend_en = !began ? g_head + b : real ? g_energy + gi + gl : g_tail + b;
                 pend_en_v = Q;
             }
             // ---- commit (uniform)
