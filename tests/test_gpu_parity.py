@@ -194,6 +194,38 @@ def test_small_groupings(m, keys):
     compare_attribution(c, key_capacity=len(vocab), label=f"small grouping m{m} keys{keys}")
 
 
+@pytest.mark.parametrize("keys", [12_289, 24_580])
+def test_many_keys_over_large_chunks(keys):
+    """Chunks too large for registers and more keys than one workgroup's table
+    holds (12,288 ids for the sums, 10,240 for M2): every id range of every
+    chunk is counted once.  The oracle adds the call's own energies per key in
+    fp64 (some 175 or 350 of one sign per key: error below 1e-13)."""
+    import torch
+    import paper_2512_08365_amd as mag
+    m = 4_300_000
+    g = torch.Generator(device="cuda").manual_seed(keys)
+    t = torch.arange(200_001, device="cuda", dtype=torch.float64)
+    P = torch.rand(200_001, generator=g, device="cuda", dtype=torch.float32) * 300.0
+    cuts = torch.arange(2 * m, device="cuda", dtype=torch.float64) * (200_000.0 / (2 * m))
+    idx = torch.randint(0, keys, (m,), generator=g, device="cuda")
+    idx[:keys] = torch.randperm(keys, generator=g, device="cuda")
+    key = idx * 7 - 3 * keys
+    per, pk, summ = mag.attribute(t, P, cuts[0::2].contiguous(), cuts[1::2].contiguous(), key,
+                                  key_capacity=keys)
+    assert summ["n_keys"] == keys
+    en = per["energy"]
+    order = torch.from_numpy(np.argsort((np.arange(keys) * 7 - 3 * keys).astype(np.uint64))).cuda()
+    cnt = torch.zeros(keys, dtype=torch.int64, device="cuda").index_add_(
+        0, idx, torch.ones_like(idx))
+    tot = torch.zeros(keys, dtype=torch.float64, device="cuda").index_add_(0, idx, en)
+    dev = en - (tot / cnt)[idx]
+    m2 = torch.zeros(keys, dtype=torch.float64, device="cuda").index_add_(0, idx, dev * dev)
+    assert torch.equal(pk["keys"], (order * 7 - 3 * keys))
+    assert torch.equal(pk["count"], cnt[order])
+    np.testing.assert_allclose(pk["sum"].cpu().numpy(), tot[order].cpu().numpy(), rtol=1e-12)
+    np.testing.assert_allclose(pk["m2"].cpu().numpy(), m2[order].cpu().numpy(), rtol=1e-12)
+
+
 def test_extreme_keys():
     c = synth.tiny_case(5, n=500, streams=2, per_stream=60)
     m = c["s"].shape[0]
