@@ -516,15 +516,20 @@ struct Job {
     // Tiles [b_begin, b_end) of a trace with `nseg` segments and `NT` tiles
     // (any larger value while the trace's end is unknown); sample g of the
     // trace is t[g - base], P[g - base].
+    // n_before samples before base are at the front of the staging buffer.
     hipError_t run_tiles(const double* t, const float* P, int64_t base, int64_t b_begin,
                          int64_t b_end, int64_t nseg, int64_t NT, hipEvent_t ev_start = nullptr,
-                         hipEvent_t ev_stop = nullptr)
+                         hipEvent_t ev_stop = nullptr, int64_t n_before = 0)
     {
         if (b_end <= b_begin) return hipSuccess;
         mag::TileParams tp{};
         tp.t = t;
         tp.P = P;
         tp.base = base;
+        if (n_before > 0) {
+            tp.t_before = w.stage_t + n_before;
+            tp.P_before = w.stage_P + n_before;
+        }
         tp.nseg = nseg;
         tp.n_total = nseg + 1;
         tp.tile_begin = b_begin;
@@ -1305,48 +1310,32 @@ int mag_stream_push(mag_stream* h, const double* t_chunk, const float* p_chunk, 
                             hipMemcpyDeviceToDevice, st)) != hipSuccess)
         return bad("bounds copy");
 
-    int64_t pos = g0;  // first sample of this chunk not yet consumed
-    while (h->n_stage > 0) {
-        // complete the staged tile b_next
-        const int64_t take = std::min<int64_t>(T + 1 - h->n_stage, g1 - pos);
-        if (take > 0) {
-            if ((e = stage(h->n_stage, pos, take)) != hipSuccess) return bad("staging copy");
-            h->n_stage += take;
-            pos += take;
-        }
-        if (h->n_stage < T + 1 || pos >= g1) {
-            h->received = g1;  // wait for more samples
-            return MAG_OK;
-        }
-        const int64_t b = h->b_next;
-        if ((e = job.run_tiles(job.w.stage_t, job.w.stage_P, b * T, b, b + 1, full,
-                               unknown_end)) != hipSuccess)
-            return bad("tile kernel");
-        h->b_next = b + 1;
-        if (pos - 1 >= g0) {
-            // the next tile starts inside this chunk
-            h->n_stage = 0;
-            pos -= 1;
-        } else {
-            // its first sample is the staged tile's last one
-            if ((e = mag::launch_stage_copy(job.w.stage_t, job.w.stage_t + T, job.w.stage_P,
-                                            job.w.stage_P + T, 1, st)) != hipSuccess)
-                return bad("staging copy");
-            h->n_stage = 1;
-        }
-    }
-    // pos == b_next * TILE lies in this chunk: run in place every tile with a
-    // sample after it in this chunk (tile b needs b*T + T + 1 <= g1 - 1)
+    // run every tile with a sample after it in this chunk (tile b needs
+    // b*T + T + 1 <= g1 - 1); those that begin before the chunk take their first
+    // samples from the staging buffer, which holds all of [b_next*T, g0)
     const int64_t b0 = h->b_next;
     int64_t b1 = b0;
     if (g1 - 2 - T >= 0) b1 = std::max<int64_t>(b0, (g1 - 2 - T) / T + 1);
-    if (b1 > b0) {
-        if ((e = job.run_tiles(t_chunk, p_chunk, g0, b0, b1, full, unknown_end)) != hipSuccess)
-            return bad("tile kernel");
-        h->b_next = b1;
+    if (b1 == b0) {
+        // no tile yet (at most T + 1 samples since b_next*T)
+        if ((e = stage(h->n_stage, g0, n_chunk)) != hipSuccess) return bad("staging copy");
+        h->n_stage += n_chunk;
+        h->received = g1;
+        return MAG_OK;
     }
-    const int64_t first = h->b_next * T;
-    if ((e = stage(0, first, g1 - first)) != hipSuccess) return bad("staging copy");
+    if ((e = job.run_tiles(t_chunk, p_chunk, g0, b0, b1, full, unknown_end, nullptr, nullptr,
+                           h->n_stage)) != hipSuccess)
+        return bad("tile kernel");
+    h->b_next = b1;
+    // what the next tile has so far: this chunk's samples from b1*T on, after
+    // the staged tile's last sample where that one begins it
+    const int64_t first = b1 * T, kept = std::max<int64_t>(g0 - first, 0);
+    if (kept > 0 && (e = mag::launch_stage_copy(job.w.stage_t, job.w.stage_t + (first - b0 * T),
+                                                job.w.stage_P, job.w.stage_P + (first - b0 * T),
+                                                kept, st)) != hipSuccess)
+        return bad("staging copy");
+    if ((e = stage(kept, first + kept, g1 - first - kept)) != hipSuccess)
+        return bad("staging copy");
     h->n_stage = g1 - first;
     h->received = g1;
     return MAG_OK;

@@ -296,7 +296,7 @@ struct SampleRegs {
 __device__ __forceinline__ bool vector_tile(int b)
 {
     const KArgs k = kargs();
-    return k->aligned16 && (int64_t)b * T + T <= k->nseg;
+    return k->aligned16 && (int64_t)b * T >= k->base && (int64_t)b * T + T <= k->nseg;
 }
 
 __device__ __forceinline__ void sample_prefetch(SampleRegs& r, int b, int lane)
@@ -362,8 +362,9 @@ __device__ __forceinline__ double sample_stage(const SampleRegs& r, int b, int L
         double tl = 0.0;
 #pragma unroll
         for (int u = 0; u <= C; ++u) {
-            tv[u] = (u <= have) ? kk->t[g + u] : tl;
-            pv[u] = (u <= have) ? kk->P[g + u] : 0.0f;
+            const bool before = g + u < 0;
+            tv[u] = (u <= have) ? (before ? kk->t_before : kk->t)[g + u] : tl;
+            pv[u] = (u <= have) ? (before ? kk->P_before : kk->P)[g + u] : 0.0f;
             tl = tv[u];
         }
     }
@@ -447,7 +448,8 @@ __global__ __launch_bounds__(WAVE) void k_tile(const TileParams p)
         // GS-ary search: one dependent load per level for all streams)
         constexpr int GS = WAVE / SP;
         const int ga = lane / GS, gl = lane % GS;  // the lane's stream and rank in its group
-        const double tau0 = p.t[(int64_t)b0 * T - p.base];
+        const int64_t g0 = (int64_t)b0 * T - p.base;
+        const double tau0 = (g0 < 0 ? p.t_before : p.t)[g0];
         const int64_t goff = (ga < S) ? p.ss.off[ga] : 0;
         int64_t lo = 0, hi = (ga < S) ? 2 * (p.ss.off[ga + 1] - goff) : 0;
         const uint64_t gmask = (GS == WAVE) ? ~0ull : ((1ull << (GS & 63)) - 1ull);
@@ -955,7 +957,8 @@ __global__ __launch_bounds__(WAVE) void k_tile_seq(const TileParams p)
     // cursor at the first tile: endpoints <= its start time (64-ary search)
     int64_t sq;
     {
-        const double tau0 = p.t[(int64_t)b0 * T - p.base];
+        const int64_t g0 = (int64_t)b0 * T - p.base;
+        const double tau0 = (g0 < 0 ? p.t_before : p.t)[g0];
         int64_t lo = 0, hi = len;
         while (hi - lo > WAVE) {
             const int64_t step = (hi - lo + WAVE - 1) / WAVE;

@@ -72,6 +72,11 @@ struct StreamSet {
 struct TileParams {
     const double* t;    // sample g (global index) is t[g - base]
     const float* P;
+    // samples before base (kept from earlier chunks of a streamed trace) are
+    // t_before[g - base], the last of them at -1; a tile that has any of them
+    // is read element by element
+    const double* t_before;
+    const float* P_before;
     int64_t base;
     int64_t nseg;       // segments of the whole trace (n_samples - 1)
     int64_t n_total;    // samples of the whole trace
