@@ -400,9 +400,9 @@ static_assert((PREFIX_ALL + 4095) / 4096 <= AGG_MAX_CHUNKS, "chunks of 4,096 int
 // workgroups of one chunk are 8 apart, so that they run at the same time on the
 // same XCD (workgroups go round the XCDs in turn) and the second reading finds
 // the chunk in that L2.  50M intervals, 20,000 keys: the sums 287 us with the
-// ranges one after another, 218 us so; M2 402 us in three ranges one after
-// another, 215 us in two so (one reading of 600 MB: 97 us; what is left is the
-// latency of load and LDS passes that alternate in the one workgroup a CU holds).
+// ranges one after another, 216 us so (204 us with agg_stream's batches); M2
+// 402 us in three ranges one after another, 213 us in two so (201 us) (one
+// reading of 600 MB: 97 us).
 constexpr int N_XCD = 8;
 struct ChunkRange {
     int chunk, range;
@@ -414,6 +414,65 @@ __device__ __forceinline__ ChunkRange chunk_range()
 static dim3 chunk_range_grid(int nchunks, unsigned ranges)
 {
     return dim3(N_XCD * ranges, (unsigned)((nchunks + N_XCD - 1) / N_XCD));
+}
+
+// A chunk's intervals, AGG_PIPE per thread at a time, the next ones requested
+// while these go into the LDS table.  take() gets a batch with its ids
+// relative to r0 (unsigned: at least the range's length for an interval of
+// another range, of no key, or past the chunk's end, which has no energy).
+// The ids stay 32 bits wide and whole batches need no test per entry: four
+// waves a SIMD (one workgroup fills the LDS) do not hide the latency of a
+// branch per interval.
+constexpr int AGG_PIPE = 8;
+struct AggBatch {
+    uint32_t sl[AGG_PIPE];
+    double en[AGG_PIPE];
+};
+__device__ __forceinline__ void agg_request(const GroupParams& p, int64_t i0, int64_t hi, AggBatch& b)
+{
+#pragma unroll
+    for (int k = 0; k < AGG_PIPE; ++k) {
+        const int64_t i = min(i0 + (int64_t)k * AGG_THREADS, hi - 1);  // (past the end: cleared below)
+        b.sl[k] = p.slot[i];
+        b.en[k] = p.energy[i];
+    }
+    asm volatile("" ::: "memory");  // requested here, ahead of the other batch's use
+}
+
+template <class Take>
+__device__ __forceinline__ void agg_stream(const GroupParams& p, int64_t lo, int64_t hi, uint32_t r0,
+                                           Take take)
+{
+    if (lo >= hi) return;  // uniform
+    constexpr int64_t STEP = (int64_t)AGG_PIPE * AGG_THREADS;
+    auto use = [&](int64_t at, AggBatch& b) {
+        if (at + STEP > hi) {  // uniform
+#pragma unroll
+            for (int k = 0; k < AGG_PIPE; ++k)
+                if (at + k * AGG_THREADS + threadIdx.x >= hi) {
+                    b.sl[k] = NO_ID;
+                    b.en[k] = 0.0;
+                }
+        }
+        uint32_t any = 0u;
+#pragma unroll
+        for (int k = 0; k < AGG_PIPE; ++k) any |= b.sl[k];
+        if (__ballot((any & MISS) != 0u) != 0ull) {  // (NO_ID has the bit too)
+#pragma unroll
+            for (int k = 0; k < AGG_PIPE; ++k) b.sl[k] = resolve_id(p, b.sl[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < AGG_PIPE; ++k) b.sl[k] -= r0;
+        take(b);
+    };
+    AggBatch a, b;
+    agg_request(p, lo + threadIdx.x, hi, a);
+    for (int64_t at = lo; at < hi; at += 2 * STEP) {
+        agg_request(p, at + STEP + threadIdx.x, hi, b);
+        use(at, a);
+        agg_request(p, at + 2 * STEP + threadIdx.x, hi, a);
+        use(at + STEP, b);
+    }
 }
 
 // chunk of intervals -> LDS table over ids [r0, r0 + SUM_IDS) -> partial table
@@ -440,25 +499,16 @@ __global__ __launch_bounds__(AGG_THREADS) void k_agg_sum(const GroupParams p)
     __syncthreads();
     const int64_t lo = (int64_t)c * p.chunk, hi = min(lo + p.chunk, p.m);
     double ctot = 0.0;  // the chunk's total energy (all its intervals)
-    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += (int64_t)AGG_BATCH * AGG_THREADS) {
-        uint32_t sl[AGG_BATCH];
-        double en[AGG_BATCH];
+    agg_stream(p, lo, hi, (uint32_t)r0, [&](const AggBatch& b) {
 #pragma unroll
-        for (int k = 0; k < AGG_BATCH; ++k) {
-            const int64_t i = i0 + (int64_t)k * AGG_THREADS;
-            sl[k] = (i < hi) ? p.slot[i] : NO_ID;
-            en[k] = (i < hi) ? p.energy[i] : 0.0;
+        for (int k = 0; k < AGG_PIPE; ++k) {
+            ctot += b.en[k];
+            if (b.sl[k] < (uint32_t)nid) {
+                atomicAdd(&lcnt[b.sl[k]], 1u);
+                atomicAdd(&lsum[b.sl[k]], b.en[k]);
+            }
         }
-#pragma unroll
-        for (int k = 0; k < AGG_BATCH; ++k) {
-            ctot += en[k];
-            const uint32_t id = resolve_id(p, sl[k]);
-            const int64_t d = (id == NO_ID) ? -1 : (int64_t)id - r0;
-            if (d < 0 || d >= nid) continue;
-            atomicAdd(&lcnt[d], 1u);
-            atomicAdd(&lsum[d], en[k]);
-        }
-    }
+    });
     __syncthreads();
     if (cr.range == 0) {
         __shared__ double red[AGG_THREADS / 64];
@@ -546,24 +596,15 @@ __global__ __launch_bounds__(AGG_THREADS) void k_agg_m2(const GroupParams p)
     }
     __syncthreads();
     const int64_t lo = (int64_t)c * p.chunk, hi = min(lo + p.chunk, p.m);
-    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += (int64_t)AGG_BATCH * AGG_THREADS) {
-        uint32_t sl[AGG_BATCH];
-        double en[AGG_BATCH];
+    agg_stream(p, lo, hi, (uint32_t)r0, [&](const AggBatch& b) {
+        double x[AGG_PIPE];
 #pragma unroll
-        for (int k = 0; k < AGG_BATCH; ++k) {
-            const int64_t i = i0 + (int64_t)k * AGG_THREADS;
-            sl[k] = (i < hi) ? p.slot[i] : NO_ID;
-            en[k] = (i < hi) ? p.energy[i] : 0.0;
-        }
+        for (int k = 0; k < AGG_PIPE; ++k)
+            x[k] = b.en[k] - lmean[min(b.sl[k], (uint32_t)nid - 1u)];
 #pragma unroll
-        for (int k = 0; k < AGG_BATCH; ++k) {
-            const uint32_t id = resolve_id(p, sl[k]);
-            const int64_t d = (id == NO_ID) ? -1 : (int64_t)id - r0;
-            if (d < 0 || d >= nid) continue;
-            const double x = en[k] - lmean[d];
-            atomicAdd(&lm2[d], x * x);
-        }
-    }
+        for (int k = 0; k < AGG_PIPE; ++k)
+            if (b.sl[k] < (uint32_t)nid) atomicAdd(&lm2[b.sl[k]], x[k] * x[k]);
+    });
     __syncthreads();
     for (int v = threadIdx.x; v < nid; v += AGG_THREADS) p.pm2[(int64_t)c * p.cap + r0 + v] = lm2[v];
 }

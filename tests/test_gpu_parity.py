@@ -194,15 +194,17 @@ def test_small_groupings(m, keys):
     compare_attribution(c, key_capacity=len(vocab), label=f"small grouping m{m} keys{keys}")
 
 
-@pytest.mark.parametrize("keys", [12_289, 24_580])
-def test_many_keys_over_large_chunks(keys):
+# (chunks of 16,797 intervals; of 16,385, one more than two batches of all
+# threads; of 24,577, one more than three)
+@pytest.mark.parametrize("m,keys", [(4_300_000, 12_289), (4_300_000, 24_580),
+                                    (4_194_305, 12_289), (6_291_712, 12_289)])
+def test_many_keys_over_large_chunks(m, keys):
     """Chunks too large for registers and more keys than one workgroup's table
     holds (12,288 ids for the sums, 10,240 for M2): every id range of every
     chunk is counted once.  The oracle adds the call's own energies per key in
-    fp64 (some 175 or 350 of one sign per key: error below 1e-13)."""
+    fp64 (some 175 to 510 of one sign per key: error below 1e-13)."""
     import torch
     import paper_2512_08365_amd as mag
-    m = 4_300_000
     g = torch.Generator(device="cuda").manual_seed(keys)
     t = torch.arange(200_001, device="cuda", dtype=torch.float64)
     P = torch.rand(200_001, generator=g, device="cuda", dtype=torch.float32) * 300.0
