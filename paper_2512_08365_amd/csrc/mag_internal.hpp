@@ -329,7 +329,7 @@ struct SpecDesc {
 
 // a tridiagonal form's place: d, squared off-diagonals, then tri_padded(K)
 // pairs {d_i, e2_{i-1}} scaled for the counts, the scaled bounds of the
-// eigenvalues and the scale
+// eigenvalues, the scale and whether the form splits
 __host__ __device__ inline int tri_padded(int n) { return (n + 7) / 8 * 8; }
 __host__ __device__ inline double2* tri_pairs(double* tri, int n)
 {

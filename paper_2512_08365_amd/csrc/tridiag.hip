@@ -750,11 +750,18 @@ __global__ __launch_bounds__(512) void k_tri_middle(const SvdTask* tasks)
 // the Gershgorin interval of each tridiagonal form, and the form as the counts
 // read it: scaled by a power of two so that the interval lies within (-1, 1],
 // the pairs {d_i, e2_{i-1}} side by side, padded to whole steps of STURM_STEP
-// with diagonal entries above the interval (which change no count), the
-// squared off-diagonals at least 2^-200 (which moves an eigenvalue by at most
-// 2^-99 of the interval and keeps the recurrence from vanishing)
+// with diagonal entries above the interval (which change no count), and
+// whether it splits: some squared off-diagonal is below SPLIT_MIN (a diagonal
+// or block tensor, channels that are always zero)
 constexpr int STURM_STEP = 8;
 constexpr int PREP_THREADS = 256;
+// With |d_i - x| <= 5 and e2 >= SPLIT_MIN, max(|p_i|, |p_{i-1}|) of the minors'
+// recurrence falls by at most 6 / SPLIT_MIN a term (e2_{i-1} |p_{i-2}| <= |p_i| +
+// 5 |p_{i-1}|), so the STURM_STEP terms between two scalings stay above
+// 2^-(8 * 123) and none underflows
+constexpr double SPLIT_MIN = 0x1p-120;
+// an eigenvalue below this, of a form scaled to (-1, 1], counts as zero
+constexpr double STURM_LEAST = 0x1p-323;
 
 __global__ __launch_bounds__(PREP_THREADS) void k_tri_prep(const SvdTask* tasks)
 {
@@ -788,19 +795,23 @@ __global__ __launch_bounds__(PREP_THREADS) void k_tri_prep(const SvdTask* tasks)
     const double wide = span > 0.0 ? 2.0 * DBL_EPSILON : 0.0;
     double2* pairs = tri_pairs(t.tri, n);
     const int np = tri_padded(n);
+    bool small = false;
     for (int i = tid; i < np; i += PREP_THREADS) {
         double2 v = make_double2(4.0, 0.0);
         if (i < n) {
             v.x = ldexp(d[i], -ex);
-            v.y = i > 0 ? fmax(ldexp(ldexp(e2[i - 1], -ex), -ex), 0x1p-200) : 0.0;
+            v.y = i > 0 ? ldexp(ldexp(e2[i - 1], -ex), -ex) : 0.0;
+            small = small || (i > 0 && !(v.y >= SPLIT_MIN));
         }
         pairs[i] = v;
     }
+    const int split = __syncthreads_or(small ? 1 : 0);
     if (tid == 0) {
         double* b = tri_bounds(t.tri, n);
         b[0] = ldexp(glo, -ex) - wide;
         b[1] = ldexp(ghi, -ex) + wide;
         b[2] = (double)ex;
+        b[3] = split ? 1.0 : 0.0;
     }
 }
 
@@ -839,9 +850,35 @@ __device__ __forceinline__ int sturm_count(lds_pair* pairs, int steps, double x)
     return c;
 }
 
+// the same for a form that splits, whose terms may vanish: scaled at every term,
+// and a term that is zero takes the sign opposite to the one before (x counts
+// as above that minor's eigenvalue), so that the block after it starts from
+// a nonzero term.  About three times the instructions of a term above
+__device__ __forceinline__ int sturm_count_split(lds_pair* pairs, int steps, double x)
+{
+    double p = 1.0, pp = 0.0;
+    uint32_t signs = 0u;
+    int c = 0;
+    for (int i = 0; i < steps; ++i) {
+#pragma unroll
+        for (int u = 0; u < STURM_STEP; ++u) {
+            double np = fma(pairs[i * STURM_STEP + u].x - x, p, -(pairs[i * STURM_STEP + u].y * pp));
+            if (np == 0.0) np = copysign(0x1p-1000, -p);
+            const int s = -__builtin_amdgcn_frexp_exp(fmax(fabs(np), fabs(p)));
+            pp = ldexp(p, s);
+            p = ldexp(np, s);
+            signs = __builtin_amdgcn_alignbit(signs, (uint32_t)((uint64_t)__double_as_longlong(p) >> 32), 31);
+        }
+        c += __popc((signs ^ (signs >> 1)) & ((1u << STURM_STEP) - 1u));
+    }
+    return c;
+}
+
 // every eigenvalue of the tridiagonal forms, G neighbouring lanes each (a
 // power of two): a round counts at G points inside every eigenvalue's
-// interval and keeps the part that holds it, to two units of rounding.
+// interval and keeps the part that holds it, to two units of rounding.  Below
+// STURM_LEAST of the scaled span an eigenvalue is zero; a form that splits, which
+// may have many of them, finds them by one count there.
 // Counting at more points at once takes fewer, costlier rounds, so G is just
 // large enough to give every SIMD a wave.  What bounds it: the LDS reads of a
 // term's coefficients, the same for every lane, about 16 cycles for each of a
@@ -869,17 +906,25 @@ __global__ __launch_bounds__(STURM_LANES) void k_sturm(const SvdTask* tasks, int
     const double* b = tri_bounds(t.tri, n);
     double lo = b[0], hi = b[1];
     const int ex = (int)b[2];
+    const bool split = __builtin_amdgcn_readfirstlane((int)b[3]) != 0;
     const int per = STURM_LANES / G;
     // (a group of lanes past the last eigenvalue has nothing to do)
     const int k = (int)(item - t.eig0) * per + (int)threadIdx.x / G, g = threadIdx.x % G;
     bool done = k >= n;
     __syncthreads();
-    for (int it = 0; it < 160; ++it) {
-        done = done || !(hi - lo > 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 0x1p-148);
+    if (split) {
+        if (sturm_count_split((lds_pair*)staged, np / STURM_STEP, STURM_LEAST) > k)
+            done = true;  // (lo is not above zero)
+        else
+            lo = fmax(lo, STURM_LEAST);
+    }
+    for (int it = 0; it < 340; ++it) {
+        done = done || !(hi - lo > 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + STURM_LEAST);
         if (__ballot(!done) == 0ull) break;
         const double h = (hi - lo) / (double)(G + 1);
         const double x = lo + h * (double)(g + 1);
-        const int c = sturm_count((lds_pair*)staged, np / STURM_STEP, x);
+        const int c = split ? sturm_count_split((lds_pair*)staged, np / STURM_STEP, x)
+                            : sturm_count((lds_pair*)staged, np / STURM_STEP, x);
         double nlo = lo, nhi = hi;
         if (c <= k) nlo = fmax(nlo, x);
         else nhi = fmin(nhi, x);
@@ -893,7 +938,8 @@ __global__ __launch_bounds__(STURM_LANES) void k_sturm(const SvdTask* tasks, int
             hi = nhi;
         }
     }
-    if (g == 0 && k < n) t.out[n - 1 - k] = sqrt(ldexp(fmax(0.5 * (lo + hi), 0.0), ex));
+    if (g == 0 && k < n)
+        t.out[n - 1 - k] = lo <= 0.0 ? 0.0 : sqrt(ldexp(fmax(0.5 * (lo + hi), 0.0), ex));
 }
 
 // how a matrix of side n is spread over a group: rows per member (a multiple

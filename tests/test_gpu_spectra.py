@@ -262,3 +262,44 @@ def test_zero_and_diagonal_tensors():
     assert np.all(np.asarray(z[0]) == 0.0)
     _assert_spectra(d, S.invariants(D), "diagonal")
     _assert_spectra(r, S.invariants(R), "repeated diagonal")
+
+
+@pytest.mark.parametrize("K", [6, 40, 150, 300, 600, 1100])
+def test_small_values_of_diagonal_tensors(K):
+    """Values from 1 down to 1e-18 and zeros on the diagonal, in any order: the
+    Gram matrix is diagonal and exact (squares of fp32 values), so that every
+    value is its square's root to a few units of rounding, and zero is zero."""
+    rng = np.random.default_rng(K)
+    v = np.zeros(K, np.float32)
+    v[:K // 2] = np.logspace(0, -18, K // 2)
+    v = rng.permutation(v)
+    D = np.zeros((K, K + 8), np.float32)
+    D[np.arange(K), np.arange(K)] = v
+    log(f"[spectra] diagonal, small values, side {K}")
+    _, _, (got,) = _gpu_lists([D])
+    want = np.sort(v.astype(np.float64))[::-1]
+    assert np.all(got[0][want == 0] == 0.0)
+    nz = want > 0
+    # (half of the eigenvalue's two units, and the root's own)
+    assert np.abs(got[0][nz] / want[nz] - 1.0).max() <= 4 * np.finfo(float).eps
+
+
+@pytest.mark.parametrize("n1,n2", [(20, 15), (100, 50), (200, 120), (300, 330)])
+def test_small_block_of_a_block_tensor(n1, n2):
+    """Two blocks that share no row or column, the second 1e-12 of the first, and
+    rows of zeros: each block's values are as near as those of the block by
+    itself would be, and the zero rows' are zero."""
+    rng = np.random.default_rng(n1)
+    b1 = rng.standard_normal((n1, n1 + 3)).astype(np.float32)
+    b2 = (1e-12 * rng.standard_normal((n2, n2 + 5))).astype(np.float32)
+    T = np.zeros((n1 + n2 + 4, n1 + n2 + 9), np.float32)
+    T[:n1, :n1 + 3] = b1
+    T[n1:n1 + n2, n1 + 3:n1 + n2 + 8] = b2
+    log(f"[spectra] blocks of sides {n1} and {n2}")
+    _, _, (got,) = _gpu_lists([T])
+    for lo, b in ((0, b1), (n1, b2)):
+        X = b.astype(np.float64)
+        want = np.linalg.eigvalsh(X @ X.T)[::-1]
+        lam = got[0][lo:lo + len(b)] ** 2
+        assert np.abs(lam - want).max() <= 1e-12 * want[0]
+    assert np.all(got[0][n1 + n2:] == 0.0)
