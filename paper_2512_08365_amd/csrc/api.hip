@@ -197,13 +197,17 @@ int check_opts(const mag_attr_opts* opts, int64_t m, int* S, uint32_t* flags, ma
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// Per-thread records of a call's timing events and of the pinned host buffer
-// its status block is copied into, one per (device, workspace).  A record
-// whose asynchronous call is not finished yet (events recorded but not read,
-// or a status copy in flight) is never handed to another workspace: idle
-// records are recycled, least recently used first, once TIMER_KEEP of them
-// exist, and the table grows when every record is busy (up to TIMER_MAX
-// unfinished asynchronous calls per thread).
+// Per-thread records of a call's events and of the pinned host buffer that its
+// status block is sent to, one per (device, workspace).  A record whose
+// asynchronous call is not finished yet (events recorded but not read, or a
+// status block on its way) is never handed to another workspace: idle records
+// are recycled, least recently used first, once TIMER_KEEP of them exist, and
+// the table grows when every record is busy (up to TIMER_MAX unfinished
+// asynchronous calls per thread).  What a record holds is made when a call first
+// needs it (events by timed and asynchronous calls and those with a group
+// stream; pinned memory in pieces for TIMER_KEEP records), the buffer only
+// once kernels of the call are on their way: a synchronous call on a new
+// workspace makes nothing else, and its kernels do not wait for that.
 struct TimerSlot {
     int dev = -1;
     const void* ws = nullptr;
@@ -218,7 +222,7 @@ struct TimerSlot {
     // a call with a group stream: recorded after its trace integration, waited
     // for by the group stream
     hipEvent_t split = nullptr;
-    mag::Status* host_status = nullptr;  // pinned host copies of the status block(s)
+    mag::Status* host_status = nullptr;  // pinned host copies of the status block(s), or NULL
     // an asynchronous mag_diff on this workspace: what its conclusion needs
     // besides the status block (table sizes or bounds, rows asked for, whether
     // a size is read on the device)
@@ -256,39 +260,53 @@ TimerSlot* timer_slot(const void* ws, bool create)
         t = fresh.get();
         g_timers.push_back(std::move(fresh));
     }
-    for (auto& x : t->ev)
-        if (x) (void)hipEventDestroy(x);
-    mag::Status* keep = t->host_status;  // the pinned buffer and the event are reused
-    hipEvent_t keep_done = t->done, keep_split = t->split;
-    *t = TimerSlot{};
+    // (the pinned buffer is reused, and the events on the same device)
+    mag::Status* keep = t->host_status;
+    if (t->dev == dev) {
+        hipEvent_t ev[4], done = t->done, split = t->split;
+        std::copy(t->ev, t->ev + 4, ev);
+        *t = TimerSlot{};
+        std::copy(ev, ev + 4, t->ev);
+        t->done = done;
+        t->split = split;
+    } else {
+        for (hipEvent_t x : {t->ev[0], t->ev[1], t->ev[2], t->ev[3], t->done, t->split})
+            if (x) (void)hipEventDestroy(x);
+        *t = TimerSlot{};
+    }
     t->host_status = keep;
-    t->done = keep_done;
-    t->split = keep_split;
     t->used = ++g_timer_clock;
-    for (auto& x : t->ev)
-        if (hipEventCreate(&x) != hipSuccess) {
-            x = nullptr;
-            return nullptr;
-        }
-    if (!t->host_status) {
-        void* h = nullptr;
-        // (portable: a kernel of whichever GPU the workspace is on writes it)
-        if (hipHostMalloc(&h, HOST_STATUS * sizeof(mag::Status),
-                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
-            return nullptr;
-        t->host_status = static_cast<mag::Status*>(h);
-    }
-    if (!t->done && hipEventCreateWithFlags(&t->done, hipEventDisableTiming) != hipSuccess) {
-        t->done = nullptr;
-        return nullptr;
-    }
-    if (!t->split && hipEventCreateWithFlags(&t->split, hipEventDisableTiming) != hipSuccess) {
-        t->split = nullptr;
-        return nullptr;
-    }
     t->dev = dev;
     t->ws = ws;
     return t;
+}
+
+// the event of a record, made when first needed
+bool have_event(hipEvent_t& e, unsigned flags)
+{
+    if (!e && hipEventCreateWithFlags(&e, flags) != hipSuccess) e = nullptr;
+    return e != nullptr;
+}
+
+// a record's pinned buffer, made when first needed, or NULL
+mag::Status* host_buffer(TimerSlot* t)
+{
+    thread_local mag::Status* piece = nullptr;
+    thread_local size_t left = 0;
+    if (!t || t->host_status) return t ? t->host_status : nullptr;
+    if (left == 0) {
+        void* h = nullptr;
+        // (portable: a kernel of whichever GPU the workspace is on writes it)
+        if (hipHostMalloc(&h, TIMER_KEEP * HOST_STATUS * sizeof(mag::Status),
+                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+            return nullptr;
+        piece = static_cast<mag::Status*>(h);
+        left = TIMER_KEEP;
+    }
+    t->host_status = piece;
+    piece += HOST_STATUS;
+    --left;
+    return t->host_status;
 }
 
 // an asynchronous call on `ws` whose result has not been collected yet
@@ -307,6 +325,7 @@ struct EventTimer {
         if (!on) return;
         slot = timer_slot(ws, true);
         on = slot != nullptr;
+        for (int i = 0; i < 4 && on; ++i) on = have_event(slot->ev[i], hipEventDefault);
     }
     // timing is best effort: a failed event call reads as zero time, and its
     // error is cleared so that it is not reported by a later launch check
@@ -442,8 +461,7 @@ int interpret_status(const mag::Status& st, mag_key_stats* per_key, mag_summary*
 // status block to, or NULL: then the block is copied after the call instead
 mag::Status* status_target(const void* workspace)
 {
-    TimerSlot* t = timer_slot(workspace, true);
-    return t ? t->host_status : nullptr;
+    return host_buffer(timer_slot(workspace, true));
 }
 
 // a device status block on the host, `stream` synchronized: `sent` is where
@@ -487,7 +505,7 @@ int async_status(const void* workspace, const mag::Status* sent, hipStream_t str
     if (!t) return MAG_OK;
     t->pending = timed;
     t->stream = stream;
-    if (t->host_status == sent) {
+    if (t->host_status == sent && have_event(t->done, hipEventDisableTiming)) {
         hipError_t e;
         if ((e = hipEventRecord(t->done, stream)) != hipSuccess) return hip_fail(e, "event record");
         t->status_pending = true;
@@ -509,7 +527,8 @@ struct Job {
     int64_t* start_idx = nullptr;
     int64_t* end_idx = nullptr;
     hipStream_t stream = nullptr;
-    mag::Status* host = nullptr;  // status_target, where the last kernel sends the status block
+    bool send = true;             // the grouping's last kernel sends the status block to ...
+    mag::Status* host = nullptr;  // ... status_target, found once the kernels before it are queued
 
     bool validate() const { return (flags & MAG_SKIP_VALIDATE) == 0; }
 
@@ -588,6 +607,7 @@ struct Job {
 
     hipError_t grouping(uint64_t* keys_out, mag_key_stats* per_key)
     {
+        host = send ? status_target(w.status) : nullptr;
         if (pl.m == 0 || !per_key) {
             // no aggregation: one workgroup adds up the energies and the fold
             const hipError_t e2 = mag::launch_energy_total(energy, pl.m, w.fold, w.status, host, stream);
@@ -778,7 +798,7 @@ int attribute_impl(const double* timestamps, const float* power, int64_t n_sampl
     // timing (MAG_TIME_KERNELS): events 1 and 2 travel with the tile kernel's
     // dispatch, event 3 follows the call's last kernel
     EventTimer timer(!no_alloc && (job.flags & MAG_TIME_KERNELS) != 0, stream, workspace);
-    if (!no_alloc) job.host = status_target(workspace);
+    job.send = !no_alloc;
     if ((e = mag::launch_init(job.w.status, job.w.cnt_fin, (int64_t)job.pl.S * (NT + 1),
                               timestamps, n_samples, stream)) != hipSuccess)
         return hip_fail(e, "init");
@@ -794,7 +814,8 @@ int attribute_impl(const double* timestamps, const float* power, int64_t n_sampl
         // everything after the trace integration moves to the group stream,
         // which first waits for the integration
         TimerSlot* ts = timer_slot(workspace, true);
-        if (!ts || !ts->split) return fail(MAG_E_HIP, "no event for the group stream");
+        if (!ts || !have_event(ts->split, hipEventDisableTiming))
+            return fail(MAG_E_HIP, "no event for the group stream");
         if ((e = hipEventRecord(ts->split, stream)) != hipSuccess ||
             (e = hipStreamWaitEvent(opts->group_stream, ts->split, 0)) != hipSuccess)
             return hip_fail(e, "group stream event");
@@ -1047,7 +1068,6 @@ int mag_attribute_counter(const double* timestamps, const double* counter, int64
 
     hipError_t e;
     EventTimer timer((flags & MAG_TIME_KERNELS) != 0, stream, workspace);
-    job.host = status_target(workspace);
     if ((e = mag::launch_init_status(job.w.status, nullptr, 0, stream)) != hipSuccess)
         return hip_fail(e, "init");
     if ((e = mag::launch_counter(cp, stream, timer.on ? timer.slot->ev[1] : nullptr,
@@ -1440,7 +1460,6 @@ int mag_stream_end(mag_stream* h, uint64_t* keys_out, mag_key_stats* per_key, ma
     int rc = MAG_OK;
     hipError_t e;
     const int64_t n = h->received;
-    job.host = status_target(job.w.status);
     const int64_t NT = (n - 1 + mag::TILE - 1) / mag::TILE;
     if (h->failed) {
         rc = fail(MAG_E_STATE, "a previous call on this stream failed");
@@ -1662,10 +1681,11 @@ int enqueue_diff(const uint64_t* keysA, const mag_key_stats* statsA, const uint6
     c.base = static_cast<char*>(workspace);
     p.status = c.take<mag::Status>(1);
     carve_candidates(c, p.na, k, &p);
-    p.host = status_target(workspace);
     hipError_t e;
     // every field of the status block the call reads is written by its kernels
-    if ((e = mag::launch_diff(p, stream)) != hipSuccess) return hip_fail(e, "diff kernels");
+    if ((e = mag::launch_diff_join(p, stream)) != hipSuccess) return hip_fail(e, "join kernel");
+    p.host = status_target(workspace);
+    if ((e = mag::launch_diff_rank(p, stream)) != hipSuccess) return hip_fail(e, "rank kernels");
     return MAG_OK;
 }
 
@@ -1717,7 +1737,8 @@ int mag_diff_async(const uint64_t* keysA, const mag_key_stats* statsA, const uin
     // the last kernel sends the status block to the pinned buffer of the
     // workspace's record
     TimerSlot* t = timer_slot(workspace, true);
-    if (!t || !t->host_status || t->host_status != p.host)
+    if (!t || !t->host_status || t->host_status != p.host ||
+        !have_event(t->done, hipEventDisableTiming))
         return fail(MAG_E_HIP, "no host buffer for the status of an asynchronous call");
     hipError_t e;
     if ((e = hipEventRecord(t->done, stream)) != hipSuccess) return hip_fail(e, "event record");
@@ -1780,7 +1801,7 @@ int mag_diff_batch(const uint64_t* keysA, const mag_key_stats* statsA, int32_t n
     c.base = static_cast<char*>(workspace);
     mag::Status* status = c.take<mag::Status>((size_t)n_candidates);
     TimerSlot* t = n_candidates <= HOST_STATUS ? timer_slot(workspace, true) : nullptr;
-    mag::Status* sent = (t && !t->busy()) ? t->host_status : nullptr;
+    mag::Status* sent = (t && !t->busy()) ? host_buffer(t) : nullptr;
     for (int32_t i = 0; i < n_candidates; ++i) {
         ps[i].status = status + i;
         ps[i].host = sent ? sent + i : nullptr;

@@ -338,13 +338,20 @@ int64_t diff_max_candidates(int64_t na, int64_t k)
 
 namespace {
 
-// the stages of `n` comparisons that share table A (the single call: n = 1);
-// p0.n_groups join workgroups (at least one: it also checks the order of B)
+// the stages of `n` comparisons that share table A (the single call: n = 1), the
+// first and then the other two; p0.n_groups join workgroups (at least one: it
+// also checks the order of B)
 template <class A>
-void launch_stages(const A& a, const DiffParams& p0, int n, hipStream_t stream)
+void launch_join(const A& a, const DiffParams& p0, int n, hipStream_t stream)
 {
     const unsigned jb = (unsigned)p0.n_groups;
     hipLaunchKernelGGL(k_diff_join<A>, dim3(jb, 1, n), dim3(JOIN_ROWS), 0, stream, a);
+}
+
+template <class A>
+void launch_rank(const A& a, const DiffParams& p0, int n, hipStream_t stream)
+{
+    const unsigned jb = (unsigned)p0.n_groups;
     if (p0.n_slots > 0) {
         const dim3 rg(jb, (unsigned)((p0.n_groups + RANK_GROUPS - 1) / RANK_GROUPS), n);
         hipLaunchKernelGGL(k_diff_rank<A>, rg, dim3(JOIN_ROWS), 0, stream, a);
@@ -354,10 +361,15 @@ void launch_stages(const A& a, const DiffParams& p0, int n, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_diff(const DiffParams& p, hipStream_t stream)
+hipError_t launch_diff_join(const DiffParams& p, hipStream_t stream)
 {
-    OneDiff a{p};
-    launch_stages(a, p, 1, stream);
+    launch_join(OneDiff{p}, p, 1, stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_diff_rank(const DiffParams& p, hipStream_t stream)
+{
+    launch_rank(OneDiff{p}, p, 1, stream);
     return hipGetLastError();
 }
 
@@ -367,7 +379,8 @@ hipError_t launch_diff_batch(const DiffParams* p, int n, hipStream_t stream)
         const int cnt = min(DIFF_BATCH, n - c0);
         BatchDiff b{};
         for (int c = 0; c < cnt; ++c) b.p[c] = p[c0 + c];
-        launch_stages(b, p[c0], cnt, stream);
+        launch_join(b, p[c0], cnt, stream);
+        launch_rank(b, p[c0], cnt, stream);
     }
     return hipGetLastError();
 }

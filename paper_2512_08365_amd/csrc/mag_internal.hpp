@@ -431,7 +431,9 @@ hipError_t launch_counter_fold(const CounterParams& p, hipStream_t stream);
 hipError_t launch_energy_total(const double* energy, int64_t m, const double2* fold, Status* st,
                                Status* host,
                                hipStream_t stream);
-hipError_t launch_diff(const DiffParams& p, hipStream_t stream);
+// a comparison's join, then its ranking and rows (p.host may be set in between)
+hipError_t launch_diff_join(const DiffParams& p, hipStream_t stream);
+hipError_t launch_diff_rank(const DiffParams& p, hipStream_t stream);
 // comparisons per launch of a batch (their parameters travel as kernel arguments)
 constexpr int DIFF_BATCH = 8;
 // n comparisons sharing table A (p[c].ka/sa/ca/na/na_dev and k equal for all c)

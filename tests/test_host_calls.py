@@ -1,0 +1,143 @@
+"""What the library asks of the HIP runtime, in which order, and what it does
+when the runtime refuses: the library's host code runs in a child process over a
+stand-in runtime (hip_double.c) that records its calls, so no GPU is needed and
+no kernel runs."""
+import ctypes
+import importlib.util
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def double(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("double") / "hip_double.so")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-Wall", "-Werror", "-o", so,
+                           os.path.join(HERE, "hip_double.c")])
+    return so
+
+
+def _run(double, name):
+    """One of the functions below, in a process of its own (the library keeps
+    records per thread, so each starts from none)."""
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = " ".join(x for x in (env.get("LD_PRELOAD"), double) if x)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), name], env=env,
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+# ------------------------------------------------------------ in the child
+
+class Library:
+    def __init__(self):
+        spec = importlib.util.spec_from_file_location(
+            "native", os.path.join(ROOT, "paper_2512_08365_amd", "_native.py"))
+        self.N = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.N)
+        self.lib = self.N.load()
+        self.d = ctypes.CDLL(None)
+        self.d.double_log.restype = ctypes.c_char_p
+        self.next_ws = 1 << 32
+
+    def log(self):
+        return self.d.double_log().decode().splitlines()
+
+    def clear(self):
+        self.d.double_clear()
+
+    def fail(self, name, times=1):
+        self.d.double_fail(name.encode(), times)
+
+    def ws(self):
+        """A workspace that no call has used (never followed)."""
+        self.next_ws += 1 << 30
+        return self.next_ws
+
+    def ok(self, rc):
+        assert rc == 0, (rc, self.lib.mag_last_error())
+
+    def stats(self, cap):
+        s = self.N.KeyStats()
+        s.sum = s.m2 = s.count = 4096
+        s.capacity = s.n_keys = cap
+        return s
+
+    def attribute(self, ws, m=10_000, flags=0):
+        N = self.N
+        o = N.AttrOpts(1, flags | N.MAG_EQUAL_SPLIT, None)
+        return self.lib.mag_attribute(4096, 4096, 100_000, 4096, 4096, 4096, m, ctypes.byref(o), None,
+                                      4096, ctypes.byref(self.stats(64)), None, ws, 1 << 29, None)
+
+    def counter(self, ws):
+        return self.lib.mag_attribute_counter(4096, 4096, 5_000, 0.1, 4096, 4096, None, 4096, 10_000, 0,
+                                              None, 4096, ctypes.byref(self.stats(64)), None, ws,
+                                              1 << 29, None)
+
+    def rank_out(self):
+        r = self.N.RankOut()
+        r.key = r.ratio = r.energy_a = r.energy_b = r.count_a = r.count_b = 4096
+        r.capacity = 10
+        return r
+
+    def diff(self, ws):
+        a, b = self.stats(64), self.stats(64)
+        return self.lib.mag_diff(4096, ctypes.byref(a), 4096, ctypes.byref(b), 10,
+                                 ctypes.byref(self.rank_out()), ws, 1 << 29, None)
+
+    def stream(self, ws, n=5_000):
+        N = self.N
+        h = ctypes.c_void_p()
+        o = N.AttrOpts(1, N.MAG_EQUAL_SPLIT, None)
+        self.ok(self.lib.mag_stream_begin(ctypes.byref(h), n, 4096, 4096, 4096, 10_000,
+                                          ctypes.byref(o), None, 64, ws, 1 << 29, None))
+        return h
+
+    def streamed(self, ws):
+        h = self.stream(ws)
+        self.ok(self.lib.mag_stream_push(h, 4096, 4096, 5_000))
+        return self.lib.mag_stream_end(h, 4096, ctypes.byref(self.stats(64)), None)
+
+
+def first(log, what):
+    return next((i for i, x in enumerate(log) if re.search(what, x)), len(log))
+
+
+def status_record_waits_for_the_launches():
+    """A call's record of its workspace costs host time (pinned memory): it is made
+    behind kernels that run already, and an untimed synchronous call makes no event."""
+    L = Library()
+    for call, kernel in ((L.attribute, "k_fix"), (L.counter, "k_counter"), (L.diff, "k_diff_join"),
+                         (L.streamed, "k_fix")):
+        for _ in range(20):  # (a piece of pinned memory serves several workspaces)
+            L.clear()
+            L.ok(call(L.ws()))
+            log = L.log()
+            assert first(log, kernel) < len(log)
+            assert first(log, "hipHostMalloc") > first(log, kernel), log
+            assert first(log, "hipEventCreate") == len(log), log
+
+
+def pinned_memory_comes_in_one_piece():
+    L = Library()
+    n = 0
+    for _ in range(16):
+        L.ok(L.attribute(L.ws()))
+    n = sum(x.startswith("hipHostMalloc") for x in L.log())
+    assert n == 1, n
+
+
+@pytest.mark.parametrize("name", ["status_record_waits_for_the_launches",
+                                  "pinned_memory_comes_in_one_piece"])
+def test_status_record(double, name):
+    _run(double, name)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]]()
