@@ -281,10 +281,14 @@ TimerSlot* timer_slot(const void* ws, bool create)
     return t;
 }
 
-// the event of a record, made when first needed
+// the event of a record, made when first needed (a failure's error is cleared,
+// so that it is not reported by a later launch check; likewise below)
 bool have_event(hipEvent_t& e, unsigned flags)
 {
-    if (!e && hipEventCreateWithFlags(&e, flags) != hipSuccess) e = nullptr;
+    if (!e && hipEventCreateWithFlags(&e, flags) != hipSuccess) {
+        (void)hipGetLastError();
+        e = nullptr;
+    }
     return e != nullptr;
 }
 
@@ -298,8 +302,10 @@ mag::Status* host_buffer(TimerSlot* t)
         void* h = nullptr;
         // (portable: a kernel of whichever GPU the workspace is on writes it)
         if (hipHostMalloc(&h, TIMER_KEEP * HOST_STATUS * sizeof(mag::Status),
-                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
             return nullptr;
+        }
         piece = static_cast<mag::Status*>(h);
         left = TIMER_KEEP;
     }

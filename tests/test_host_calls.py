@@ -133,8 +133,23 @@ def pinned_memory_comes_in_one_piece():
     assert n == 1, n
 
 
+def calls_go_on_without_pinned_memory():
+    """The status block is then copied after the call; the failed allocation is
+    not taken for a failure of the next launch."""
+    L = Library()
+    for call in (L.attribute, L.counter, L.diff, L.streamed):
+        L.fail("hipHostMalloc", 1000)
+        L.clear()
+        L.ok(call(L.ws()))
+        log = L.log()
+        assert first(log, "hipHostMalloc failed") < first(log, "hipMemcpyAsync 96 kind 2") < len(log)
+    L.fail("hipEventCreateWithFlags")
+    L.ok(L.attribute(L.ws(), flags=L.N.MAG_TIME_KERNELS))  # untimed then
+
+
 @pytest.mark.parametrize("name", ["status_record_waits_for_the_launches",
-                                  "pinned_memory_comes_in_one_piece"])
+                                  "pinned_memory_comes_in_one_piece",
+                                  "calls_go_on_without_pinned_memory"])
 def test_status_record(double, name):
     _run(double, name)
 
