@@ -142,7 +142,7 @@ def calls_go_on_without_pinned_memory():
         L.clear()
         L.ok(call(L.ws()))
         log = L.log()
-        assert first(log, "hipHostMalloc failed") < first(log, "hipMemcpyAsync 96 kind 2") < len(log)
+        assert first(log, "hipHostMalloc failed") < first(log, "hipMemcpyAsync .* kind 2") < len(log)
     L.fail("hipEventCreateWithFlags")
     L.ok(L.attribute(L.ws(), flags=L.N.MAG_TIME_KERNELS))  # untimed then
 
