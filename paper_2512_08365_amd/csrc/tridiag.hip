@@ -945,6 +945,8 @@ __global__ __launch_bounds__(STURM_LANES) void k_sturm(const SvdTask* tasks, int
 // how a matrix of side n is spread over a group: rows per member (a multiple
 // of TG_RUN, so that the slots, n rounded up to whole members, fit the
 // threads' slots), members, and where the rows are kept
+constexpr int TG_LDS = 155 << 10;  // most LDS for a member's rows (beside TgShared)
+static_assert(TG_LDS + sizeof(TgShared) <= 160 * 1024, "LDS of one workgroup");
 struct TgShape {
     int th, q, rr, rows, G, slots, n_mem, n_lds;
 };
@@ -956,7 +958,7 @@ bool tg_fit(int n, int th, int q, int rr, int rows_max, TgShape& s)
         if (rows * G > q * th || G > 64 * tg_dots(q)) continue;
         s = TgShape{th, q, rr, rows, G, rows * G, 0, 0};
         const int out = rows - std::min(rows, rr);
-        const int lds_max = (int)((size_t)(155 << 10) / (sizeof(double) * q * th));
+        const int lds_max = (int)((size_t)TG_LDS / (sizeof(double) * q * th));
         s.n_lds = std::min(out, lds_max);
         s.n_mem = out - s.n_lds;
         return true;
@@ -974,12 +976,14 @@ bool tg_shape(int n, TgShape& s)
     return tg_fit(n, 512, 8, 8, 16, s);
 }
 
+// (a kernel's attribute belongs to the whole process: every call sets the same
+// value, so that no other thread's launch meets a smaller one)
 template <int TH, int RR, int Q>
 hipError_t launch_group(const TriGroupJobs& jobs, int wgs, int lds, int32_t* failed,
                         hipStream_t stream)
 {
     hipError_t e = hipFuncSetAttribute((const void*)k_tri_group<TH, RR, Q>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, TG_LDS);
     if (e != hipSuccess) return e;
     void* args[] = {(void*)&jobs, (void*)&failed};
     return hipLaunchCooperativeKernel((const void*)k_tri_group<TH, RR, Q>, dim3((unsigned)wgs),
@@ -1085,7 +1089,8 @@ hipError_t launch_sturm(const SvdTask* tasks, int n_tasks, int64_t n_items, int 
     if (n_tasks <= 0) return hipSuccess;
     const int lds = tri_padded(n_max) * (int)sizeof(double2);
     hipError_t e = hipFuncSetAttribute((const void*)k_sturm,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       tri_padded(SVD_MAX_K) * (int)sizeof(double2));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tri_prep, dim3((unsigned)n_tasks), dim3(PREP_THREADS), 0, stream, tasks);
     hipLaunchKernelGGL(k_sturm, dim3((unsigned)n_items), dim3(STURM_LANES), (size_t)lds, stream,

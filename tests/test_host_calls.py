@@ -105,6 +105,19 @@ class Library:
         return self.lib.mag_stream_end(h, 4096, ctypes.byref(self.stats(64)), None)
 
 
+    def invariants(self, shapes, ws=None):
+        """fp32 tensors of these shapes (never followed)"""
+        N = self.N
+        ts = (N.Tensor * len(shapes))()
+        for t, sh in zip(ts, shapes):
+            t.data, t.rank = 1 << 20, len(sh)
+            for i, x in enumerate(sh):
+                t.dims[i] = x
+        b = ctypes.c_size_t(0)
+        self.ok(self.lib.mag_invariants_workspace_size(ts, len(shapes), ctypes.byref(b)))
+        return self.lib.mag_invariants(ts, len(shapes), 1 << 20, ws or self.ws(), b.value, None)
+
+
 def first(log, what):
     return next((i for i, x in enumerate(log) if re.search(what, x)), len(log))
 
@@ -147,11 +160,28 @@ def calls_go_on_without_pinned_memory():
     L.ok(L.attribute(L.ws(), flags=L.N.MAG_TIME_KERNELS))  # untimed then
 
 
+def kernel_attributes_do_not_change():
+    """A kernel's largest LDS size is the process's: calls of any size set one value."""
+    L = Library()
+    for side in (5, 40, 130, 200, 600, 1100, 2500, 4096, 8192):
+        L.ok(L.invariants([(side, side)]))
+    values = {}
+    for x in L.log():
+        if x.startswith("hipFuncSetAttribute"):
+            _, fn, attr, v = x.split()
+            values.setdefault((fn, attr), set()).add(v)
+    assert values and all(len(v) == 1 for v in values.values()), values
+
+
 @pytest.mark.parametrize("name", ["status_record_waits_for_the_launches",
                                   "pinned_memory_comes_in_one_piece",
                                   "calls_go_on_without_pinned_memory"])
 def test_status_record(double, name):
     _run(double, name)
+
+
+def test_kernel_attributes(double):
+    _run(double, "kernel_attributes_do_not_change")
 
 
 if __name__ == "__main__":
