@@ -765,29 +765,33 @@ constexpr double STURM_LEAST = 0x1p-323;
 
 __global__ __launch_bounds__(PREP_THREADS) void k_tri_prep(const SvdTask* tasks)
 {
-    __shared__ double red[2][PREP_THREADS / 64];
+    __shared__ double red[3][PREP_THREADS / 64];
     const SvdTask& t = tasks[blockIdx.x];
     const int n = (int)t.K, tid = threadIdx.x;
     const double* d = t.tri;
     const double* e2 = t.tri + n;
-    double glo = INFINITY, ghi = -INFINITY;
+    double glo = INFINITY, ghi = -INFINITY, least = INFINITY;
     for (int i = tid; i < n; i += PREP_THREADS) {
         const double r = (i > 0 ? sqrt(e2[i - 1]) : 0.0) + (i + 1 < n ? sqrt(e2[i]) : 0.0);
         glo = fmin(glo, d[i] - r);
         ghi = fmax(ghi, d[i] + r);
+        if (i + 1 < n) least = fmin(least, e2[i]);
     }
     for (int off = 32; off > 0; off >>= 1) {
         glo = fmin(glo, __shfl_xor(glo, off));
         ghi = fmax(ghi, __shfl_xor(ghi, off));
+        least = fmin(least, __shfl_xor(least, off));
     }
     if ((tid & 63) == 0) {
         red[0][tid >> 6] = glo;
         red[1][tid >> 6] = ghi;
+        red[2][tid >> 6] = least;
     }
     __syncthreads();
     for (int v = 0; v < PREP_THREADS / 64; ++v) {
         glo = fmin(glo, red[0][v]);
         ghi = fmax(ghi, red[1][v]);
+        least = fmin(least, red[2][v]);
     }
     const double span = fmax(fabs(glo), fabs(ghi));
     // (a matrix of zeros, or one that is not finite, is left unscaled)
@@ -795,23 +799,20 @@ __global__ __launch_bounds__(PREP_THREADS) void k_tri_prep(const SvdTask* tasks)
     const double wide = span > 0.0 ? 2.0 * DBL_EPSILON : 0.0;
     double2* pairs = tri_pairs(t.tri, n);
     const int np = tri_padded(n);
-    bool small = false;
     for (int i = tid; i < np; i += PREP_THREADS) {
         double2 v = make_double2(4.0, 0.0);
         if (i < n) {
             v.x = ldexp(d[i], -ex);
             v.y = i > 0 ? ldexp(ldexp(e2[i - 1], -ex), -ex) : 0.0;
-            small = small || (i > 0 && !(v.y >= SPLIT_MIN));
         }
         pairs[i] = v;
     }
-    const int split = __syncthreads_or(small ? 1 : 0);
     if (tid == 0) {
         double* b = tri_bounds(t.tri, n);
         b[0] = ldexp(glo, -ex) - wide;
         b[1] = ldexp(ghi, -ex) + wide;
         b[2] = (double)ex;
-        b[3] = split ? 1.0 : 0.0;
+        b[3] = ldexp(ldexp(least, -ex), -ex) >= SPLIT_MIN ? 0.0 : 1.0;
     }
 }
 
