@@ -525,8 +525,10 @@ int mag_invariant_count(const mag_tensor* tensor, int32_t* n_unfoldings, int64_t
  * device-wide Householder steps, four launches each, down to 4096 (the
  * workspace then also holds about (n / 256 + 3) n doubles of scratch).  The
  * eigenvalues of all unfoldings are then bisected by waves spread over the
- * whole device.  MAG_E_HIP also when the workgroups of a group lose touch (a
- * member waited 20 s for another).
+ * whole device.  A call takes no groups on a stream with a CU mask, and goes on
+ * without them when a cooperative launch is refused or the workgroups of a
+ * group lose touch (a member waited about a second for another: a kernel that
+ * held a CU all that time kept them from running together).
  * Synchronizes `stream`.  Errors: MAG_E_NULL, MAG_E_SIZE, MAG_E_ALIGN,
  * MAG_E_WORKSPACE, MAG_E_HIP.
  */

@@ -2061,6 +2061,92 @@ bool one_workgroup_each(const InvPlan& pl)
     return !(3.3 * (double)mag::tri_group_rounds(mid.data(), (int)mid.size()) < one);
 }
 
+// whether the stream's kernels can use every CU (one with a CU mask cannot be
+// counted on to hold a group's members together)
+bool whole_device(hipStream_t stream)
+{
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    int n = 0;
+    for (uint32_t x : mask) n += __builtin_popcount(x);
+    return n == 0 || n >= mag::device_cu_count();
+}
+
+// the spectra of the planned tensors, waited for; groups_ok: sides above
+// TRI_MIDDLE may be reduced by groups of workgroups.  *lost: a group could not
+// be launched or lost touch, and the spectra are not complete
+int run_invariants(InvPlan& pl, const InvWorkspace& w, double* spectra, hipStream_t stream,
+                   bool groups_ok, bool* lost)
+{
+    *lost = false;
+    int64_t go = 0, to = 0, wo = 0;
+    const bool one_each = !groups_ok || one_workgroup_each(pl);
+    bool small = false, middle = false;
+    std::vector<mag::TriMatrix> groups;
+    for (size_t i = 0; i < pl.tasks.size(); ++i) {
+        mag::SvdTask& t = pl.tasks[i];
+        const int K = (int)t.K;
+        t.gram = w.gram + go;
+        t.out = spectra + pl.spec_off[i];
+        go += t.K * t.K;
+        t.tri = w.tri + to;
+        to += mag::tri_len(K);
+        small = small || K <= mag::TRI_SMALL;
+        middle = middle || (K > mag::TRI_SMALL && K <= mag::TRI_MIDDLE);
+        if (K < mag::SVD_GROUP_MIN) continue;
+        const int side = group_side(K), k0 = K - side;
+        if (groups_ok && !(one_each && K <= mag::SVD_SMALL_K) && mag::tri_group_fits(side))
+            groups.push_back(mag::TriMatrix{t.gram + (size_t)k0 * K + k0, t.tri + k0,
+                                            t.tri + K + k0, w.words + wo, K, side, 0u});
+        wo += mag::tri_group_words(side);
+    }
+    std::sort(groups.begin(), groups.end(),
+              [](const mag::TriMatrix& a, const mag::TriMatrix& b) { return a.n > b.n; });
+    int32_t* failed = reinterpret_cast<int32_t*>(w.words + pl.n_words);
+    hipError_t e;
+    if ((e = hipMemcpyAsync(w.tasks, pl.tasks.data(), sizeof(mag::SvdTask) * pl.tasks.size(),
+                            hipMemcpyHostToDevice, stream)) != hipSuccess)
+        return hip_fail(e, "task copy");
+    if ((e = mag::launch_svd(w.tasks, (int)pl.tasks.size(), pl.n_narrow, pl.n_items_narrow,
+                             pl.n_whole, pl.n_items_whole, pl.n_items, one_each, w.gram,
+                             w.clear_len, stream)) != hipSuccess)
+        return hip_fail(e, "invariant kernels");
+    if ((e = mag::launch_tri_one(w.tasks, (int)pl.tasks.size(), small, middle, stream)) != hipSuccess)
+        return hip_fail(e, "reduction kernels");
+    // sides beyond the groups' reach: device-wide steps down to it (or, where no
+    // group can run, all the way)
+    for (const auto& t : pl.tasks) {
+        if (t.K <= mag::SVD_SMALL_K) continue;
+        const int K = (int)t.K, side = group_side(K);
+        const int stop = groups_ok && mag::tri_group_fits(side) ? K - side : K - 2;
+        if (stop > 0 && (e = mag::launch_svd_large(t.gram, K, stop, w.large, t.tri, t.tri + K,
+                                                   stream)) != hipSuccess)
+            return hip_fail(e, "large unfolding kernels");
+    }
+    int32_t apart = 0;
+    if (!groups.empty()) {
+        if (mag::launch_tri_groups(groups.data(), (int)groups.size(), -1, failed, stream) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            *lost = true;
+            return MAG_OK;
+        }
+        if ((e = hipMemcpyAsync(&apart, failed, sizeof(apart), hipMemcpyDeviceToHost, stream)) !=
+            hipSuccess)
+            return hip_fail(e, "status copy");
+    }
+    if ((e = mag::launch_sturm(w.tasks, (int)pl.tasks.size(), pl.n_eig_items, pl.eig_lanes,
+                               pl.max_k, stream)) != hipSuccess)
+        return hip_fail(e, "eigenvalue kernels");
+    // (the task table on the host stays alive until the copy is done)
+    if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "synchronize");
+    *lost = apart != 0;
+    return MAG_OK;
+}
+
 // spectra descriptors of a tensor set: offsets in the order mag_invariants writes
 int spec_descs(const mag_tensor* ts, int32_t n, std::vector<mag::SpecDesc>& out)
 {
@@ -2126,66 +2212,13 @@ int mag_invariants(const mag_tensor* tensors, int32_t n_tensors, double* spectra
     const size_t need = carve_invariants(pl, nullptr, w);
     if (workspace_bytes < need) return fail(MAG_E_WORKSPACE, "workspace too small");
     carve_invariants(pl, workspace, w);
-    int64_t go = 0, to = 0, wo = 0;
-    const bool one_each = one_workgroup_each(pl);
-    bool small = false, middle = false;
-    std::vector<mag::TriMatrix> groups;
-    for (size_t i = 0; i < pl.tasks.size(); ++i) {
-        mag::SvdTask& t = pl.tasks[i];
-        const int K = (int)t.K;
-        t.gram = w.gram + go;
-        t.out = spectra + pl.spec_off[i];
-        go += t.K * t.K;
-        t.tri = w.tri + to;
-        to += mag::tri_len(K);
-        small = small || K <= mag::TRI_SMALL;
-        middle = middle || (K > mag::TRI_SMALL && K <= mag::TRI_MIDDLE);
-        if (K < mag::SVD_GROUP_MIN) continue;
-        const int side = group_side(K), k0 = K - side;
-        if (!(one_each && K <= mag::SVD_SMALL_K) && mag::tri_group_fits(side))
-            groups.push_back(mag::TriMatrix{t.gram + (size_t)k0 * K + k0, t.tri + k0,
-                                            t.tri + K + k0, w.words + wo, K, side, 0u});
-        wo += mag::tri_group_words(side);
-    }
-    std::sort(groups.begin(), groups.end(),
-              [](const mag::TriMatrix& a, const mag::TriMatrix& b) { return a.n > b.n; });
-    int32_t* failed = reinterpret_cast<int32_t*>(w.words + pl.n_words);
-    hipError_t e;
-    if ((e = hipMemcpyAsync(w.tasks, pl.tasks.data(), sizeof(mag::SvdTask) * pl.tasks.size(),
-                            hipMemcpyHostToDevice, stream)) != hipSuccess)
-        return hip_fail(e, "task copy");
-    if ((e = mag::launch_svd(w.tasks, (int)pl.tasks.size(), pl.n_narrow, pl.n_items_narrow,
-                             pl.n_whole, pl.n_items_whole, pl.n_items, one_each, w.gram,
-                             w.clear_len, stream)) != hipSuccess)
-        return hip_fail(e, "invariant kernels");
-    if ((e = mag::launch_tri_one(w.tasks, (int)pl.tasks.size(), small, middle, stream)) != hipSuccess)
-        return hip_fail(e, "reduction kernels");
-    // sides beyond the groups' reach: device-wide steps down to it (or, on a
-    // device with too few CUs for the group, all the way)
-    for (const auto& t : pl.tasks) {
-        if (t.K <= mag::SVD_SMALL_K) continue;
-        const int K = (int)t.K, side = group_side(K);
-        const int stop = mag::tri_group_fits(side) ? K - side : K - 2;
-        if (stop > 0 && (e = mag::launch_svd_large(t.gram, K, stop, w.large, t.tri, t.tri + K,
-                                                   stream)) != hipSuccess)
-            return hip_fail(e, "large unfolding kernels");
-    }
-    int32_t lost = 0;
-    if (!groups.empty()) {
-        if ((e = mag::launch_tri_groups(groups.data(), (int)groups.size(), failed, stream)) !=
-            hipSuccess)
-            return hip_fail(e, "reduction kernels");
-        if ((e = hipMemcpyAsync(&lost, failed, sizeof(lost), hipMemcpyDeviceToHost, stream)) !=
-            hipSuccess)
-            return hip_fail(e, "status copy");
-    }
-    if ((e = mag::launch_sturm(w.tasks, (int)pl.tasks.size(), pl.n_eig_items, pl.eig_lanes,
-                               pl.max_k, stream)) != hipSuccess)
-        return hip_fail(e, "eigenvalue kernels");
-    // (the task table on the host stays alive until the copy is done)
-    if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "synchronize");
-    if (lost) return fail(MAG_E_HIP, "the workgroups of a reduction lost touch");
-    return MAG_OK;
+    bool lost = false;
+    rc = run_invariants(pl, w, spectra, stream,
+                        pl.max_k < mag::SVD_GROUP_MIN || whole_device(stream), &lost);
+    // a group that could not be launched, or whose members were not all resident
+    // (another kernel held a CU): once more without groups
+    if (rc == MAG_OK && lost) rc = run_invariants(pl, w, spectra, stream, false, &lost);
+    return rc;
 }
 
 int mag_match_workspace_size(int32_t na, int32_t nb, size_t* bytes)

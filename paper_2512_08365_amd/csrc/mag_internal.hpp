@@ -393,8 +393,12 @@ hipError_t launch_tri_one(const SvdTask* tasks, int n_tasks, bool small, bool mi
 bool tri_group_fits(int n);
 int tri_group_rounds(const int* n, int count);
 // tridiagonal forms by groups of workgroups (m is used up); *failed (zeroed)
-// becomes nonzero if members lost touch
-hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream_t stream);
+// becomes nonzero if members lost touch: the matrices are then used up for
+// nothing, and whatever of the launches has not run yet leaves at once.
+// lost_at: the step of a launch at which member 0 of every group leaves as if it
+// had waited too long (-1: never; for tests)
+hipError_t launch_tri_groups(TriMatrix* m, int count, int lost_at, int32_t* failed,
+                             hipStream_t stream);
 // Householder steps 0 .. stop - 1 of one n x n matrix, each four launches over
 // the whole device (stop = n - 2: the whole reduction, with the last corner);
 // scratch of svd_large_scratch(n) doubles

@@ -21,8 +21,10 @@
 // it has read all of step k - 1's, whose writers had by then read step
 // k - 2's.  The words start at zero, which no step carries.  Every poll is
 // bounded in time; a member that gives up marks the call failed and leaves,
-// and the others follow within the same bound.  The members are launched
-// cooperatively (all resident together).
+// and the others follow when their own waits end, about a second in all (a look
+// at the mark in the polls cost every step 1 %).  The members are launched
+// cooperatively (all resident together; the runtime puts cooperative launches
+// of several streams one after the other).
 //
 // What bounds it: the exchange, about 2 us for 8 members and 3.4 us for 256 (a
 // probe that exchanges n doubles and does nothing else), then the latency of
@@ -46,7 +48,9 @@ namespace {
 constexpr int TG_WAVES = 8;  // most waves of a member
 constexpr int TG_RUN = 4;  // consecutive slots of one member (one 64-byte piece of words)
 constexpr int TG_MAX_ROWS = 16;  // rows of one member, all kinds
-constexpr uint64_t TG_PATIENCE = 20ull * 100000000ull;  // 20 s of the 100 MHz wall clock
+// 0.25 s of the 100 MHz wall clock for one wait; the waits of a step (four to
+// six, an exchange takes microseconds) follow one another
+constexpr uint64_t TG_PATIENCE = 25000000ull;
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_row(double v)
@@ -235,7 +239,8 @@ struct TgShared {
 // Every wave reads p_{k+1} and the members' parts of p.u itself, which leaves
 // two workgroup barriers a step: for A u, and for the tail's norm.
 template <int TH, int RR, int Q>
-__global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32_t* failed)
+__global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int lost_at,
+                                                  int32_t* failed)
 {
     constexpr int WV = TH / 64;
     constexpr int RC = RR * Q <= 64 ? 8 : 4;  // register rows handled at a time
@@ -314,9 +319,10 @@ __global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32
     // x: row k after step k - 1; the first one as it is
     double x[Q], u[Q], w[Q], un[Q];
     double tail = 0.0;
-    if (tid == 0) sm.dead = 0;
+    if (tid == 0) sm.dead = *(volatile int32_t*)failed;  // (by a launch before this one)
     if (tid < TG_MAX_ROWS + 2) sm.us[0][tid] = sm.us[1][tid] = sm.ws[0][tid] = sm.ws[1][tid] = 0.0;
     __syncthreads();
+    if (sm.dead) return;  // uniform
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         x[q] = col[q] >= 0 ? A[col[q]] : 0.0;
@@ -330,7 +336,8 @@ __global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32
     __syncthreads();
 
     int m1 = 1 % G, j1 = 1 / G;  // member and local row of row k + 1
-    for (int k = 0; k < job.stop; ++k) {
+    const int steps = (mem == 0 && lost_at >= 0) ? min(lost_at, job.stop) : job.stop;
+    for (int k = 0; k < steps; ++k) {
         const uint32_t tag = job.tag0 + (uint32_t)k + 1;
         uint64_t* const now = words + (tag & 1) * wstep;
         const int cur = k & 1, prev = cur ^ 1;
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(TH) void k_tri_group(const TriGroupJobs jobs, int32
             }
         }
     }
+    if (steps < job.stop && tid == 0) atomicOr(failed, 1);
 }
 
 // One workgroup of W waves per matrix, for sides up to min(W R, 64 C): lane l
@@ -980,13 +988,13 @@ bool tg_shape(int n, TgShape& s)
 // (a kernel's attribute belongs to the whole process: every call sets the same
 // value, so that no other thread's launch meets a smaller one)
 template <int TH, int RR, int Q>
-hipError_t launch_group(const TriGroupJobs& jobs, int wgs, int lds, int32_t* failed,
-                        hipStream_t stream)
+hipError_t launch_group(const TriGroupJobs& jobs, int wgs, int lds, int lost_at,
+                        int32_t* failed, hipStream_t stream)
 {
     hipError_t e = hipFuncSetAttribute((const void*)k_tri_group<TH, RR, Q>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, TG_LDS);
     if (e != hipSuccess) return e;
-    void* args[] = {(void*)&jobs, (void*)&failed};
+    void* args[] = {(void*)&jobs, (void*)&lost_at, (void*)&failed};
     return hipLaunchCooperativeKernel((const void*)k_tri_group<TH, RR, Q>, dim3((unsigned)wgs),
                                       dim3(TH), args, (unsigned)lds, stream);
 }
@@ -1019,7 +1027,8 @@ int tri_group_rounds(const int* n, int count)
 // smaller class, its rows go back to memory and a smaller group takes over (a
 // step costs less the fewer members exchange words and the fewer slots a
 // thread has), together with the matrices of the batch that start there.
-hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream_t stream)
+hipError_t launch_tri_groups(TriMatrix* m, int count, int lost_at, int32_t* failed,
+                             hipStream_t stream)
 {
     const int cus = device_cu_count();
     const int limits[] = {SVD_GROUP_MAX, 3072, 2048, 1024, 512, 0};
@@ -1051,11 +1060,11 @@ hipError_t launch_tri_groups(TriMatrix* m, int count, int32_t* failed, hipStream
             if (jobs.count == 0) break;
             hipError_t e;
             switch (cls) {
-            case 512: e = launch_group<256, 16, 2>(jobs, wgs, lds, failed, stream); break;
-            case 1024: e = launch_group<512, 16, 2>(jobs, wgs, lds, failed, stream); break;
-            case 2048: e = launch_group<512, 16, 4>(jobs, wgs, lds, failed, stream); break;
-            case 3072: e = launch_group<512, 8, 6>(jobs, wgs, lds, failed, stream); break;
-            default: e = launch_group<512, 8, 8>(jobs, wgs, lds, failed, stream); break;
+            case 512: e = launch_group<256, 16, 2>(jobs, wgs, lds, lost_at, failed, stream); break;
+            case 1024: e = launch_group<512, 16, 2>(jobs, wgs, lds, lost_at, failed, stream); break;
+            case 2048: e = launch_group<512, 16, 4>(jobs, wgs, lds, lost_at, failed, stream); break;
+            case 3072: e = launch_group<512, 8, 6>(jobs, wgs, lds, lost_at, failed, stream); break;
+            default: e = launch_group<512, 8, 8>(jobs, wgs, lds, lost_at, failed, stream); break;
             }
             if (e != hipSuccess) return e;
         }

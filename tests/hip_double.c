@@ -13,7 +13,7 @@ typedef int err_t;
 static char g_log[1 << 20];
 static size_t g_len;
 static char g_fail[64];
-static int g_fail_left;
+static int g_fail_left, g_fail_after;
 static err_t g_sticky;
 static uint32_t g_word;          /* what a 4-byte copy to the host brings, once */
 static uint32_t g_cu_mask[8];
@@ -32,7 +32,7 @@ static void note(const char* fmt, ...)
 }
 static err_t call(const char* name)
 {
-    if (g_fail_left > 0 && !strcmp(name, g_fail)) {
+    if (g_fail_left > 0 && !strcmp(name, g_fail) && g_fail_after-- <= 0) {
         --g_fail_left;
         g_sticky = 2;
         note("%s failed\n", name);
@@ -50,10 +50,11 @@ static const char* fn_name(const void* f)
 /* for the test */
 const char* double_log(void) { return g_log; }
 void double_clear(void) { g_len = 0; g_log[0] = 0; }
-void double_fail(const char* name, int times)
+void double_fail(const char* name, int times, int after)
 {
     snprintf(g_fail, sizeof(g_fail), "%s", name);
     g_fail_left = times;
+    g_fail_after = after;
 }
 void double_word(uint32_t w) { g_word = w; }
 void double_cu_mask(const uint32_t* m) { memcpy(g_cu_mask, m, sizeof(g_cu_mask)); g_mask_set = 1; }

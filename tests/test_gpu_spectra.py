@@ -7,6 +7,7 @@ tridiagonal reduction and bisection are backward stable, so the error is far
 below that).  Matching: the GPU's decisions equal the oracle's on the same
 spectra, and planted permutations match while perturbed tensors do not.
 """
+import ctypes
 import itertools
 
 import numpy as np
@@ -303,3 +304,86 @@ def test_small_block_of_a_block_tensor(n1, n2):
         lam = got[0][lo:lo + len(b)] ** 2
         assert np.abs(lam - want).max() <= 1e-12 * want[0]
     assert np.all(got[0][n1 + n2:] == 0.0)
+
+
+class _TriMatrix(ctypes.Structure):
+    _fields_ = [("A", ctypes.c_void_p), ("d", ctypes.c_void_p), ("e2", ctypes.c_void_p),
+                ("words", ctypes.c_void_p), ("lda", ctypes.c_int64), ("n", ctypes.c_int32),
+                ("tag", ctypes.c_uint32)]
+
+
+@pytest.mark.parametrize("sides,lost_at", [((600,), 0), ((600, 300), 40), ((1100, 700), 75),
+                                           ((300,), -1)])
+def test_members_that_lose_touch_leave(sides, lost_at):
+    """One member of every group leaves at a step, as if it had waited too long:
+    the others follow within about a second, the launch that would have taken over does
+    at once, and the call is marked.  Never lost: the tridiagonal form has the
+    matrix's eigenvalues."""
+    import time
+
+    import torch
+    from paper_2512_08365_amd import _native
+    launch = getattr(_native.load(),
+                     "_ZN3mag17launch_tri_groupsEPNS_9TriMatrixEiiPiP12ihipStream_t")
+    rng = np.random.default_rng(lost_at + 2)
+    log(f"[spectra] groups {sides} lose a member at step {lost_at}")
+    keep, m = [], (_TriMatrix * len(sides))()
+    for t, n in zip(m, sides):
+        X = rng.standard_normal((n, n))
+        A = torch.from_numpy(X + X.T).cuda()
+        d, e2 = (torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(2))
+        words = torch.zeros(8 * (4096 + 128), dtype=torch.int64, device="cuda")
+        keep.append((A.clone(), A, d, e2, words))
+        t.A, t.d, t.e2, t.words = A.data_ptr(), d.data_ptr(), e2.data_ptr(), words.data_ptr()
+        t.lda, t.n, t.tag = n, n, 0
+    failed = torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    rc = launch(m, len(sides), lost_at, ctypes.c_void_p(failed.data_ptr()),
+                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0 and time.perf_counter() - t0 < 1.8
+    assert bool(failed.item()) == (lost_at >= 0)
+    if lost_at < 0:
+        for A0, _, d, e2, _ in keep:
+            off = e2[:-1].sqrt()
+            T = torch.diag(d) + torch.diag(off, 1) + torch.diag(off, -1)
+            got, want = torch.linalg.eigvalsh(T.cpu()), torch.linalg.eigvalsh(A0.cpu())
+            assert float((got - want).abs().max()) <= 1e-12 * float(want.abs().max())
+    # the next call is as any other
+    T = rng.standard_normal((300, 320)).astype(np.float32)
+    _, _, (got,) = _gpu_lists([T])
+    _assert_spectra(got, S.invariants(T), "after")
+
+
+def test_invariants_of_two_threads():
+    """Two host threads, each with a stream of its own, whose groups fill the
+    device by themselves: every call's spectra are its own."""
+    import threading
+
+    import torch
+    import paper_2512_08365_amd as mag
+    rng = np.random.default_rng(17)
+    sets = [[rng.standard_normal((512, 530)).astype(np.float32) for _ in range(8)] +
+            [rng.standard_normal((20, 1000)).astype(np.float32)],
+            [rng.standard_normal((1500, 1600)).astype(np.float32), np.eye(40, 50, dtype=np.float32)]]
+    dev = [[torch.from_numpy(x).cuda() for x in s] for s in sets]
+    want = [mag.invariants(ts)[0].cpu().numpy() for ts in dev]
+    got = [[], []]
+    log("[spectra] two threads")
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(4):
+                got[i].append(mag.invariants(dev[i])[0].cpu().numpy())
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert len(got[i]) == 4
+        for g in got[i]:  # (the order in which a Gram matrix's chunks are added differs)
+            np.testing.assert_allclose(g ** 2, want[i] ** 2, rtol=0, atol=1e-12 * want[i].max() ** 2)

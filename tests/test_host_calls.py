@@ -52,8 +52,8 @@ class Library:
     def clear(self):
         self.d.double_clear()
 
-    def fail(self, name, times=1):
-        self.d.double_fail(name.encode(), times)
+    def fail(self, name, times=1, after=0):
+        self.d.double_fail(name.encode(), times, after)
 
     def ws(self):
         """A workspace that no call has used (never followed)."""
@@ -173,6 +173,54 @@ def kernel_attributes_do_not_change():
     assert values and all(len(v) == 1 for v in values.values()), values
 
 
+def _reductions(log):
+    """Which reductions a call launched: groups, device-wide steps, one workgroup
+    from memory; and how many times the Gram matrices were cleared."""
+    return (sum(x.startswith("cooperative") for x in log), any("k_hh_reflector" in x for x in log),
+            any("k_svd_eig" in x for x in log), sum("k_svd_clear" in x for x in log))
+
+
+SIDES = [(600, 700), (300, 310), (130, 140)]
+
+
+def groups_where_they_fit():
+    L = Library()
+    L.ok(L.invariants(SIDES))
+    coop, steps, one, passes = _reductions(L.log())
+    assert coop > 0 and not steps and not one and passes == 1
+
+
+def without_groups_when_the_launch_is_refused():
+    L = Library()
+    for before in (0, 1):  # (1: the second launch is refused, the matrices half reduced)
+        L.clear()
+        L.fail("hipLaunchCooperativeKernel", 1, before)
+        L.ok(L.invariants(SIDES))
+        log = L.log()
+        coop, steps, one, passes = _reductions(log[first(log, "CooperativeKernel failed"):])
+        assert coop == 0 and steps and one and passes == 1, log
+        assert _reductions(log)[3] == 2
+
+
+def without_groups_when_members_lose_touch():
+    L = Library()
+    L.d.double_word(1)  # (the call's only 4-byte copy to the host)
+    L.ok(L.invariants(SIDES))
+    log = L.log()
+    again = len(log) - 1 - first(log[::-1], "k_svd_clear")
+    coop, steps, one, passes = _reductions(log[again:])
+    assert coop == 0 and steps and one and passes == 1, log
+    assert _reductions(log)[3] == 2 and _reductions(log)[0] > 0
+
+
+def without_groups_on_a_masked_stream():
+    L = Library()
+    L.d.double_cu_mask((ctypes.c_uint32 * 8)(*[0xffffffff] * 7 + [0x7fffffff]))
+    L.ok(L.invariants(SIDES))
+    coop, steps, one, passes = _reductions(L.log())
+    assert coop == 0 and steps and one and passes == 1
+
+
 @pytest.mark.parametrize("name", ["status_record_waits_for_the_launches",
                                   "pinned_memory_comes_in_one_piece",
                                   "calls_go_on_without_pinned_memory"])
@@ -182,6 +230,14 @@ def test_status_record(double, name):
 
 def test_kernel_attributes(double):
     _run(double, "kernel_attributes_do_not_change")
+
+
+@pytest.mark.parametrize("name", ["groups_where_they_fit",
+                                  "without_groups_when_the_launch_is_refused",
+                                  "without_groups_when_members_lose_touch",
+                                  "without_groups_on_a_masked_stream"])
+def test_group_reductions(double, name):
+    _run(double, name)
 
 
 if __name__ == "__main__":
