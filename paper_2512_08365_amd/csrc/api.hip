@@ -1561,8 +1561,10 @@ int mag_stream_state_import(mag_stream* h, const void* host_buf, size_t bytes)
         return fail(MAG_E_STATE, "state was exported from a stream begun with other arguments");
     const size_t need = state_bytes(h);
     if (hd.bytes_total != need || bytes < need) return fail(MAG_E_SIZE, "state buffer size mismatch");
-    if (hd.received < 0 || hd.received > j.pl.n || hd.b_next < 0 || hd.n_stage < 0 ||
-        hd.n_stage > mag::TILE + 1)
+    // (the staging buffer holds all samples from the next tile's first one on)
+    if (hd.received < 0 || hd.received > j.pl.n || hd.b_next < 0 || hd.b_next > j.pl.NT ||
+        hd.n_stage < 0 || hd.n_stage > mag::TILE + 1 ||
+        hd.n_stage != hd.received - hd.b_next * mag::TILE)
         return fail(MAG_E_STATE, "corrupt stream state");
     const char* in = static_cast<const char*>(host_buf);
     size_t off = sizeof(hd);

@@ -221,6 +221,32 @@ def without_groups_on_a_masked_stream():
     assert coop == 0 and steps and one and passes == 1
 
 
+def stream_states_are_checked():
+    """A state whose counts of samples, tiles and staged samples do not agree is
+    refused: the next push would read its staging buffer by their difference."""
+    import struct
+    L = Library()
+    for pushed in (0, 300, 513, 514, 5_000):
+        a = L.stream(L.ws(), n=10_000)
+        if pushed:
+            L.ok(L.lib.mag_stream_push(a, 4096, 4096, pushed))
+        n = ctypes.c_size_t(0)
+        L.ok(L.lib.mag_stream_state_export(a, None, ctypes.byref(n)))
+        buf = ctypes.create_string_buffer(n.value)
+        L.ok(L.lib.mag_stream_state_export(a, buf, ctypes.byref(n)))
+        at = 40  # magic, three sizes, streams and flags; then received, b_next, n_stage
+        received, b_next, n_stage = struct.unpack_from("<3q", buf.raw, at)
+        assert received == pushed and n_stage == received - 512 * b_next
+        L.ok(L.lib.mag_stream_state_import(L.stream(L.ws(), n=10_000), buf, n.value))
+        for bad in ((received, b_next, n_stage + 1), (received + 1, b_next, n_stage),
+                    (received, b_next + 1, n_stage), (received, b_next, max(n_stage - 1, 0) + 2 * (n_stage == 0)),
+                    (received, 1 << 54, n_stage)):
+            bb = ctypes.create_string_buffer(buf.raw, n.value)
+            struct.pack_into("<3q", bb, at, *bad)
+            rc = L.lib.mag_stream_state_import(L.stream(L.ws(), n=10_000), bb, n.value)
+            assert rc == L.N.MAG_E_STATE, (pushed, bad, rc)
+
+
 @pytest.mark.parametrize("name", ["status_record_waits_for_the_launches",
                                   "pinned_memory_comes_in_one_piece",
                                   "calls_go_on_without_pinned_memory"])
@@ -238,6 +264,10 @@ def test_kernel_attributes(double):
                                   "without_groups_on_a_masked_stream"])
 def test_group_reductions(double, name):
     _run(double, name)
+
+
+def test_stream_states(double):
+    _run(double, "stream_states_are_checked")
 
 
 if __name__ == "__main__":
