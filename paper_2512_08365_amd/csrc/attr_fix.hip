@@ -57,7 +57,8 @@ __device__ void fix_cross(const FixParams& p, int64_t idx)
         atomicOr(&p.status->err, ERR_INTERVAL);
     }
     // an interval is active at the tile's start, and this is the first such tile
-    const bool mine = in && (c0 & 1) && c0 <= len && cprev != c0;
+    // (a cursor outside the stream, from an imported state, names no interval)
+    const bool mine = in && (c0 & 1) && c0 > 0 && c0 <= len && cprev != c0;
     if (__ballot(mine) == 0ull) return;
     double E = 0.0;
     bool more = false;  // the interval goes on past the batch

@@ -228,6 +228,35 @@ def test_stream_errors():
     torch.cuda.synchronize()
 
 
+def test_imported_cursor_outside_its_stream():
+    """A cursor below zero in an imported state (of the second of two streams)
+    names no interval: nothing is written in front of the stream's energies."""
+    import struct
+
+    import paper_2512_08365_amd as mag
+    c = synth.long_trace(23, 6000, 2, 40)
+    d = to_gpu(c)
+    off = [int(x) for x in c["offsets"]]
+    log("[case] imported cursor outside its stream")
+    kw = dict(n_streams=2, stream_offsets=off, validate=False)
+    energies = []
+    for corrupt in (False, True):
+        st = mag.Stream(6000, d["s"], d["e"], d["key"], **kw)
+        st.push(d["t"][:4000], d["P"][:4000])
+        state = bytearray(bytes(st.export_state()))
+        st.abort()
+        if corrupt:
+            # header and status block of 88 bytes each, then the cursors, one
+            # row of tiles (and one more) a stream
+            ld = (6000 - 1 + TILE - 1) // TILE
+            struct.pack_into("<q", state, 176 + 8 * ((ld + 1) + 3), -3)
+        st = mag.Stream(6000, d["s"], d["e"], d["key"], **kw)
+        st.import_state(bytes(state))
+        st.push(d["t"][4000:], d["P"][4000:])
+        energies.append(st.end()[0]["energy"].cpu().numpy())
+    assert np.array_equal(energies[0][:off[1]], energies[1][:off[1]])
+
+
 @pytest.mark.slow
 def test_long_run_workload_both_sides_streamed_in_32M_chunks():
     """The hour-long workload (360,000,000 samples at 100 kHz, 50,000,000
