@@ -280,6 +280,75 @@ def test_key_capacity_error():
     assert ei.value.code == -3
 
 
+# one grouping each: one workgroup, lookups inside the aggregation (its smallest and
+# largest), the id pass with chunks in registers, and with chunks read in passes
+@pytest.mark.parametrize("m", [4_000, 4_097, 262_144, 262_145, 4_194_305])
+@pytest.mark.parametrize("cap", [100, 2_000])
+def test_key_capacity_error_of_every_grouping(m, cap):
+    """3,000 distinct keys: more than a table for 100 keys has slots (1,024), and
+    more than 2,000 rows of capacity but not than its slots (4,096).  Both are
+    refused, and the same workspace then serves a call whose keys fit."""
+    import torch
+    import paper_2512_08365_amd as mag
+    from paper_2512_08365_amd import _native as N
+    g = torch.Generator(device="cuda").manual_seed(m)
+    t = torch.arange(50_001, device="cuda", dtype=torch.float64)
+    P = torch.rand(50_001, generator=g, device="cuda", dtype=torch.float32) * 300.0
+    cuts = torch.arange(2 * m, device="cuda", dtype=torch.float64) * (50_000.0 / (2 * m))
+    s, e = cuts[0::2].contiguous(), cuts[1::2].contiguous()
+    idx = torch.randint(0, 3_000, (m,), generator=g, device="cuda")
+    idx[:3_000] = torch.randperm(3_000, generator=g, device="cuda")
+    ws = torch.empty(mag.workspace_size(50_001, m, cap), dtype=torch.uint8, device="cuda")
+    log(f"[case] key capacity {cap} for 3,000 keys of {m} intervals")
+    with pytest.raises(mag.MagnetonError) as ei:
+        mag.attribute(t, P, s, e, idx, key_capacity=cap, workspace=ws)
+    assert ei.value.code == N.MAG_E_CAPACITY
+    key = idx % 100
+    per, pk, summ = mag.attribute(t, P, s, e, key, key_capacity=cap, workspace=ws)
+    assert summ["n_keys"] == 100
+    en, k = per["energy"].cpu().numpy(), key.cpu().numpy()
+    assert np.array_equal(pk["keys"].cpu().numpy(), np.arange(100))
+    assert np.array_equal(pk["count"].cpu().numpy(), np.bincount(k))
+    np.testing.assert_allclose(pk["sum"].cpu().numpy(), np.bincount(k, weights=en), rtol=1e-10)
+
+
+@pytest.mark.parametrize("m,keys", [(300_000, 500), (4_300_000, 12_289), (4_194_305, 2)])
+def test_dominant_keys(m, keys):
+    """Two fifths of the intervals on one key and a fifth on another (the first and
+    the last id, of one id range or of two): the LDS adds of a chunk's wave go to
+    one address.  A chunk has at most 16,797 intervals and there are at most 256
+    chunks: 1.9e-12 of the sum if every rounding of a cell went one way; the
+    oracle adds on the host with a 64-bit mantissa (1e-13 at most)."""
+    import torch
+    import paper_2512_08365_amd as mag
+    rng = np.random.default_rng(keys)
+    t = torch.arange(200_001, device="cuda", dtype=torch.float64)
+    P = torch.from_numpy(rng.random(200_001, dtype=np.float32) * np.float32(300.0)).cuda()
+    cuts = torch.arange(2 * m, device="cuda", dtype=torch.float64) * (200_000.0 / (2 * m))
+    idx = rng.integers(0, keys, m)
+    draw = rng.random(m)
+    idx[draw < 0.4] = 0
+    idx[draw > 0.8] = keys - 1
+    idx[:keys] = rng.permutation(keys)
+    log(f"[case] dominant keys: m={m} keys={keys}")
+    per, pk, summ = mag.attribute(t, P, cuts[0::2].contiguous(), cuts[1::2].contiguous(),
+                                  torch.from_numpy(idx * 7).cuda(), key_capacity=keys)
+    assert summ["n_keys"] == keys
+    en = per["energy"].cpu().numpy().astype(np.longdouble)
+    order = np.argsort(idx, kind="stable")
+    cnt = np.bincount(idx, minlength=keys)
+    first = np.concatenate([[0], np.cumsum(cnt)[:-1]])
+    tot = np.add.reduceat(en[order], first)
+    m2 = np.add.reduceat((en - (tot / cnt)[idx])[order] ** 2, first)
+    assert np.array_equal(pk["keys"].cpu().numpy(), np.arange(keys) * 7)
+    assert np.array_equal(pk["count"].cpu().numpy(), cnt)
+    np.testing.assert_allclose(pk["sum"].cpu().numpy(), tot.astype(float), rtol=2e-12)
+    # (beside the sum's own rounding, a difference E - mean is off by a rounding
+    # of E: m2 is of the order of the sum of E squared)
+    second = m2 + cnt * (tot / cnt) ** 2
+    assert np.all(np.abs(pk["m2"].cpu().numpy() - m2) <= 2e-12 * second)
+
+
 def test_device_detected_errors():
     import paper_2512_08365_amd as mag
     import torch
