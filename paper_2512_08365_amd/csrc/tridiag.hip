@@ -952,37 +952,43 @@ __global__ __launch_bounds__(STURM_LANES) void k_sturm(const SvdTask* tasks, int
 }
 
 // how a matrix of side n is spread over a group: rows per member (a multiple
-// of TG_RUN, so that the slots, n rounded up to whole members, fit the
-// threads' slots), members, and where the rows are kept
+// of TG_RUN), members, and where the rows are kept
 constexpr int TG_LDS = 155 << 10;  // most LDS for a member's rows (beside TgShared)
 static_assert(TG_LDS + sizeof(TgShared) <= 160 * 1024, "LDS of one workgroup");
 struct TgShape {
-    int th, q, rr, rows, G, slots, n_mem, n_lds;
+    int th, q, rows, G, slots, n_mem, n_lds;
 };
 
-bool tg_fit(int n, int th, int q, int rr, int rows_max, TgShape& s)
+// classes by slots per thread: sides up to th * q take the first that they fit.
+// n rounded up to whole members fits the slots, for rows divides them; the
+// smallest group (side 193) has 13 members, the largest 256
+struct TgClass {
+    int th, q, rr, rows;
+};
+constexpr TgClass TG_CLASS[] = {
+    {256, 2, 16, 16}, {512, 2, 16, 16}, {512, 4, 16, 16}, {512, 6, 8, 12}, {512, 8, 8, 16}};
+constexpr bool tg_classes_fit()
 {
-    for (int rows = rows_max; rows >= TG_RUN; rows -= TG_RUN) {
-        const int G = (n + rows - 1) / rows;
-        if (rows * G > q * th || G > 64 * tg_dots(q)) continue;
-        s = TgShape{th, q, rr, rows, G, rows * G, 0, 0};
-        const int out = rows - std::min(rows, rr);
-        const int lds_max = (int)((size_t)TG_LDS / (sizeof(double) * q * th));
-        s.n_lds = std::min(out, lds_max);
-        s.n_mem = out - s.n_lds;
-        return true;
+    int top = 0;
+    for (const TgClass& c : TG_CLASS) {
+        const int slots = c.th * c.q;
+        if (slots <= top || slots % c.rows || c.rows % TG_RUN || c.rows > TG_MAX_ROWS ||
+            slots / c.rows > 64 * tg_dots(c.q) || c.th > 64 * TG_WAVES)
+            return false;
+        top = slots;
     }
-    return false;
+    return top == SVD_GROUP_MAX;
 }
+static_assert(tg_classes_fit(), "rows, members and slots of the classes");
 
-// classes by slots per thread
-bool tg_shape(int n, TgShape& s)
+TgShape tg_shape(int n)
 {
-    if (n <= 512 && tg_fit(n, 256, 2, 16, 16, s)) return true;
-    if (n <= 1024 && tg_fit(n, 512, 2, 16, 16, s)) return true;
-    if (n <= 2048 && tg_fit(n, 512, 4, 16, 16, s)) return true;
-    if (n <= 3072 && tg_fit(n, 512, 6, 8, 12, s)) return true;
-    return tg_fit(n, 512, 8, 8, 16, s);
+    int i = 0;
+    while (n > TG_CLASS[i].th * TG_CLASS[i].q) ++i;  // n <= SVD_GROUP_MAX
+    const TgClass& c = TG_CLASS[i];
+    const int G = (n + c.rows - 1) / c.rows, out = c.rows - std::min(c.rows, c.rr);
+    const int n_lds = std::min(out, TG_LDS / (int)(sizeof(double) * c.q * c.th));
+    return TgShape{c.th, c.q, c.rows, G, c.rows * G, out - n_lds, n_lds};
 }
 
 // (a kernel's attribute belongs to the whole process: every call sets the same
@@ -1003,8 +1009,7 @@ hipError_t launch_group(const TriGroupJobs& jobs, int wgs, int lds, int lost_at,
 
 bool tri_group_fits(int n)
 {
-    TgShape s;
-    return n >= SVD_GROUP_MIN && n <= SVD_GROUP_MAX && tg_shape(n, s) && s.G <= device_cu_count();
+    return n >= SVD_GROUP_MIN && n <= SVD_GROUP_MAX && tg_shape(n).G <= device_cu_count();
 }
 
 int tri_group_rounds(const int* n, int count)
@@ -1012,13 +1017,12 @@ int tri_group_rounds(const int* n, int count)
     const int cus = device_cu_count();
     int rounds = 1, used = 0;
     for (int i = 0; i < count; ++i) {
-        TgShape s;
-        if (!tg_shape(n[i], s)) return 1 << 20;
-        if (used + s.G > cus) {
+        const int G = tg_shape(n[i]).G;
+        if (used + G > cus) {
             ++rounds;
             used = 0;
         }
-        used += s.G;
+        used += G;
     }
     return rounds;
 }
@@ -1039,12 +1043,10 @@ hipError_t launch_tri_groups(TriMatrix* m, int count, int lost_at, int32_t* fail
             int wgs = 0, lds = 0, cls = -1;
             for (; i < count && jobs.count < TRI_GROUP_JOBS; ++i) {
                 if (m[i].n <= next || m[i].n > top) continue;
-                TgShape s;
-                if (m[i].n < 3 || !tg_shape(m[i].n, s) || s.G > cus) return hipErrorInvalidValue;
+                const TgShape s = tg_shape(m[i].n);
+                if (m[i].n < SVD_GROUP_MIN || s.G > cus) return hipErrorInvalidValue;
                 if ((cls >= 0 && s.th * s.q != cls) || wgs + s.G > cus) break;
                 cls = s.th * s.q;
-                // (a matrix that its members' rounding pushed a class up runs on
-                // to the class after the next)
                 const int n = m[i].n, stop = next > 0 ? n - next : n - 2;
                 jobs.job[jobs.count++] =
                     TriGroupJob{m[i].A, m[i].d, m[i].e2, m[i].words, m[i].lda, n, s.G, wgs, s.slots,

@@ -208,10 +208,10 @@ def test_register_reduced_sides(K):
     _assert_spectra(got, S.invariants(T), f"side {K}")
 
 
-# Sides of the group reduction's classes and their edges: the smallest, sides
-# whose rows per member change to fit the slots (489, 505, 1017), whole
-# classes, and one past each (reduced in two classes, one taking over from the
-# other); 3073 and above keep some rows in LDS and in memory
+# Sides of the group reduction's classes and their edges: the smallest, one member
+# with one row more than the others (257), members without their last rows (489,
+# 505, 1017), whole classes, and one past each (reduced in two classes, one taking
+# over from the other); above 2048 some rows are in LDS, above 3072 in memory too
 @pytest.mark.parametrize("K", [193, 194, 257, 489, 505, 512, 513, 1017, 1024, 1025, 2048, 2049])
 def test_group_reduced_sides(K):
     rng = np.random.default_rng(K)
