@@ -306,6 +306,40 @@ def test_small_block_of_a_block_tensor(n1, n2):
     assert np.all(got[0][n1 + n2:] == 0.0)
 
 
+def test_one_workgroup_each_in_a_large_batch():
+    """Many sides in (192, 512]: one workgroup each, from memory, where groups would
+    take several launches after one another."""
+    rng = np.random.default_rng(64)
+    Ts = [rng.standard_normal((200 + i % 3, 215)).astype(np.float32) for i in range(64)]
+    log("[spectra] 64 sides of 200 to 202")
+    _, _, got = _gpu_lists(Ts)
+    for i, (T, g) in enumerate(zip(Ts, got)):
+        _assert_spectra(g, S.invariants(T), f"large batch {i}")
+
+
+@pytest.mark.parametrize("n", [3, 300, 700, 1030])
+def test_device_wide_reduction_alone(n):
+    """The device-wide steps all the way (where no group can run: a masked stream,
+    a refused launch): the tridiagonal form has the matrix's eigenvalues."""
+    import torch
+    from paper_2512_08365_amd import _native
+    launch = getattr(_native.load(), "_ZN3mag16launch_svd_largeEPdiiS0_S0_S0_P12ihipStream_t")
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, n))
+    A = torch.from_numpy(X + X.T).cuda()
+    want = np.linalg.eigvalsh(X + X.T)
+    d, e2 = (torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(2))
+    scratch = torch.zeros((2 + (n + 255) // 256) * n + 8, dtype=torch.float64, device="cuda")
+    log(f"[spectra] device-wide reduction of side {n}")
+    rc = launch(ctypes.c_void_p(A.data_ptr()), n, n - 2, ctypes.c_void_p(scratch.data_ptr()),
+                ctypes.c_void_p(d.data_ptr()), ctypes.c_void_p(e2.data_ptr()),
+                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    off = np.sqrt(e2.cpu().numpy()[:-1])
+    T = np.diag(d.cpu().numpy()) + np.diag(off, 1) + np.diag(off, -1)
+    assert np.abs(np.linalg.eigvalsh(T) - want).max() <= 1e-12 * np.abs(want).max()
+
+
 class _TriMatrix(ctypes.Structure):
     _fields_ = [("A", ctypes.c_void_p), ("d", ctypes.c_void_p), ("e2", ctypes.c_void_p),
                 ("words", ctypes.c_void_p), ("lda", ctypes.c_int64), ("n", ctypes.c_int32),
