@@ -3,23 +3,27 @@
 // The key table (keys and ids) and the rank counters are cleared by k_fix,
 // the launch before.
 //
-// 1. k_key_insert: the distinct keys of a prefix of the intervals go into an
-//    open-addressing hash table (linear probing, 64-bit compare-and-swap; the
-//    all-ones key is kept out of band in slot H so any uint64 is a legal key).
-//    A slot is 16 bytes, {key, id}, so a lookup reads both from one line.
-//    Each workgroup de-duplicates its part of the prefix in LDS first.
+// 1. k_key_insert: the distinct keys of a prefix of the intervals (the first
+//    PREFIX_ALL) go into an open-addressing hash table (linear probing, 64-bit
+//    compare-and-swap; the all-ones key is kept out of band in slot H so any
+//    uint64 is a legal key).  A slot is 16 bytes, {key, id}, so a lookup reads
+//    both from one line.  Each workgroup de-duplicates its part of the prefix
+//    in LDS first.
 // 2. k_compact: every occupied slot without an id takes the next dense id (its
 //    place in the distinct-key list).
 // 3. k_keymap: the id of every interval's key, found with plain cached loads
 //    (the table and the ids come from earlier launches).  A key first seen
 //    after the prefix is inserted and recorded as MISS | slot; k_compact, run
-//    again, gives it an id, which the aggregation passes look up.
+//    again, gives it an id, which the aggregation passes look up.  Neither runs
+//    where the prefix is the whole call and a chunk has at most 4,096 intervals:
+//    the aggregation (k_agg_one<true>) then probes the table itself.
 // 4. k_rank: rank of each key = number of smaller keys (its row in the output,
 //    ascending by key).
 // 5. k_agg_sum / k_fin_sum: each workgroup aggregates one chunk of intervals
 //    into an LDS table indexed by id (count, sum); the partial tables are
 //    reduced per key in chunk order, and the key, count and sum written to the
-//    key's row.  Per-workgroup atomics add the rows into the attributed energy.
+//    key's row.  The chunks' total energies are stored and added up by the first
+//    workgroup of the reduction.
 // 6. k_agg_m2 / k_fin_m2: second pass over the chunk for sum (E - mean)^2
 //    (the two-pass definition of M2).
 // When a chunk fits one batch of loads per thread (up to AGG_THREADS *
@@ -30,9 +34,9 @@
 // sum_c n_c (mean_c - mean)^2 (every term non-negative).
 // Up to GROUP_SMALL intervals one workgroup does all of it (k_group_small).
 // Plain stores carry every partial result: device-scope atomics, which are
-// slow on this part, are used only for counters, inserts and one add per
-// workgroup.  Every thread requests all the loads of a batch before it uses
-// any of them, so a pass costs about one memory latency per batch.
+// slow on this part, are used only for counters and inserts.  Every thread
+// requests all the loads of a batch before it uses any of them, so a pass costs
+// about one memory latency per batch.
 
 #include "mag_internal.hpp"
 
@@ -922,7 +926,11 @@ __global__ __launch_bounds__(FO_THREADS) void k_fin_one(const GroupParams p)
 // map, the ranks, count, sum, M2 about the mean, latency, the totals), where
 // seven launches after one another would each cost more than the work: 2,000
 // intervals of 50 keys 32 us in seven kernels, 12 us here.  Bound by the latency
-// of its LDS passes; above GS_MAX the table would not fit beside the sums.
+// of its LDS passes and, above GS_COUNTED keys, of the sort's (78 stages at 4,096
+// keys).  Whole calls, seven kernels and this one: 2,000 intervals of 50, 257
+// and 2,000 keys 78, 87 and 117 us, 56, 67 and 81 us; 4,096 intervals of 257,
+// 1,024 and 4,096 keys 92, 105 and 120 us, 71, 77 and 113 us.  Above GS_MAX the
+// table would not fit beside the sums.
 // ---------------------------------------------------------------------------
 constexpr int GS_THREADS = 1024;
 constexpr int GS_MAX = GROUP_SMALL;
@@ -944,7 +952,6 @@ struct GroupSmall {
     uint32_t cnt[GS_MAX];
     uint32_t wtot[GS_THREADS / 64];
     double red[3 * GS_THREADS / 64];
-    uint32_t nu;
     int special;
 };
 static_assert(sizeof(GroupSmall) <= 156 * 1024, "LDS of one workgroup");
