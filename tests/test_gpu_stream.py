@@ -249,7 +249,7 @@ def test_imported_cursor_outside_its_stream():
             # header and status block of 88 bytes each, then the cursors, one
             # row of tiles (and one more) a stream
             ld = (6000 - 1 + TILE - 1) // TILE
-            struct.pack_into("<q", state, 176 + 8 * ((ld + 1) + 3), -3)
+            struct.pack_into("<q", state, 176 + 8 * ((ld + 1) + 3), -21)
         st = mag.Stream(6000, d["s"], d["e"], d["key"], **kw)
         st.import_state(bytes(state))
         st.push(d["t"][4000:], d["P"][4000:])
