@@ -7,8 +7,8 @@
 2. The library's host code (argument checks, workspace planning, the host
    side of every entry point, the subgraph matching in graph.hip), built by
    hipcc with both sanitizers on the host compilation only, under the CPU
-   tests that drive it (the ABI checks and the subgraph matching; clang's ASan
-   runtime preloaded).
+   tests that drive it (the ABI checks, the host calls over a stand-in runtime
+   and the subgraph matching; clang's ASan runtime preloaded).
 
 Undefined behaviour aborts the run (-fno-sanitize-recover); leak checking is
 off (Python's own allocations are not ours).  Usage:
@@ -74,6 +74,7 @@ def main() -> int:
         env = base_env(clang_runtime())
         env["MAG_LIBRARY_SO"] = lib
         rc |= run([sys.executable, "-m", "pytest", "tests/test_abi.py", "tests/test_graph_match.py",
+                   "tests/test_host_calls.py",
                    "-q", "-x", "-p", "no:cacheprovider"], env)
     print(f"[sanitize] {'clean' if rc == 0 else 'FAILED'}", flush=True)
     return rc
