@@ -518,7 +518,7 @@ int mag_invariant_count(const mag_tensor* tensor, int32_t* n_unfoldings, int64_t
  * exactly; MFMA products), reduced to tridiagonal form and bisected; an
  * eigenvalue is within about 1e-13 of the largest (relative), so a singular
  * value far below the largest carries an absolute error near 3e-7 of it.
- * Gram sides up to 128 (up to 512 where a batch holds many) are reduced by one
+ * Gram sides up to 192 (up to 512 where a batch holds many) are reduced by one
  * workgroup each, all unfoldings side by side; sides up to 4096 by groups of
  * workgroups that keep the matrix on the chip and run all together
  * (cooperative launches); larger ones (up to MAG_SVD_MAX_K) first take

@@ -1144,11 +1144,12 @@ int mag_attribute_finish(const void* workspace, mag_key_stats* per_key, mag_summ
 // chunked streaming
 //
 // The trace arrives as consecutive chunks.  Tiles are the same as in the
-// one-shot call (tile b covers samples b*TILE .. b*TILE + TILE); a tile whose
-// samples all lie in one chunk runs in place, a tile spanning two or more
-// chunks is assembled in a staging buffer first.  A tile runs only once a
-// sample beyond it has arrived, so the trace's last tile (the only one that
-// may be short, and the one that records the final cursors) runs at the end.
+// one-shot call (tile b covers samples b*TILE .. b*TILE + TILE).  A push runs, in
+// one launch, every tile with a sample beyond it in this chunk; the first of
+// them may have begun in earlier chunks: its samples from there are read from
+// a staging buffer, to which a push copies those of the tile it leaves
+// unfinished.  The trace's last tile (the only one that may be short, and the one
+// that records the final cursors) runs at the end, from the staging buffer.
 // Everything carried from chunk to chunk lives in the workspace: per-tile
 // cursors and partial energies, the staging buffer and the status block.
 // ---------------------------------------------------------------------------
