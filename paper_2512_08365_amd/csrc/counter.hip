@@ -10,21 +10,33 @@
 // segment before e_i.
 //
 // Work layout.  One 64-lane wave per chunk of 64 consecutive windows (lane l
-// owns window 64c + l).  For valid input every endpoint of the chunk's windows
-// has its lower bound in [J, K], J = lower_bound(u, first start) and K =
-// lower_bound(u, last end).  Up to CNT_STREAM readings between them are
-// streamed through LDS in blocks of 256 (4 coalesced loads per lane), each
-// endpoint resolved by a binary search inside the block that holds its lower
-// bound; over more (windows far apart: the blocks would follow one another, a
-// memory latency each) every lane searches its two endpoints in memory.  J and
-// K come from one probe of 64 readings around the position a uniform reading
-// rate predicts, then a 64-ary search when the probe misses (irregular
-// readings).  The readings themselves are checked by workgroups of their own,
-// in equal pieces: a chunk's wave that checked the readings up to the next
-// chunk's first one took 130 blocks in a row where the counter was read on for
-// a tenth of the session after its last window (98,304 windows, 340,000
-// readings: 180 us, 9.4 us now).  The kernel is bound by memory latency at the
-// sizes of replay sessions.
+// owns window 64c + l).  With J_c = lower_bound(u, s_{64c}), chunk c owns the
+// readings [J_c, J_{c+1}), the last chunk those up to K = lower_bound(u, last
+// end); for valid input every endpoint of its windows has its lower bound among
+// them or at J_{c+1}.  Up to `most` of them are streamed through LDS in blocks
+// of 256 (4 coalesced loads per lane) and checked on the way, each endpoint
+// resolved by a binary search inside the block that holds its lower bound.
+// Over more (windows far apart: the blocks would follow one another, a memory
+// latency each) every lane searches its two endpoints in memory, and the
+// readings are left to the fold launch, whose workgroups then check the whole
+// trace in equal pieces.  The J come from one probe of 64 readings around the
+// position a uniform reading rate predicts, then a 64-ary search when the probe
+// misses (irregular readings).  The readings before J_0 and after the last K are
+// checked by workgroups of their own beside the chunks: where the last chunk's
+// wave checked them, it took 130 blocks in a row in a counter read on for a
+// tenth of the session after its last window (98,304 windows, 340,000 readings:
+// 180 us, 9.4 us now).  The J_c need not increase for every reading to be
+// checked: the [J_c, J_{c+1}) together leave out none between J_0 and the last
+// one, and a chunk that does not stream says so to the fold launch.  Where there
+// are more readings than the chunks would stream, the workgroups beside them
+// check all from the start and a chunk reads up to its last window's end.
+// At the sizes of replay sessions the kernel is bound by memory latency; long
+// ones read every reading once.  Whole calls of 1,000,000 windows over 50M and
+// 100M readings 280 and 425 us (a second reading by workgroups that check
+// everything: 416 and 700 us), of 64,000 over 6.4M 113 us (172 us streamed by the
+// chunks alone), of 10,000 over 100M 440 us (4.9 ms).
+
+#include <algorithm>
 
 #include <hip/hip_ext.h>
 
@@ -37,9 +49,18 @@ constexpr int WAVE = 64;
 constexpr int PER_LANE = CNT_BLOCK / WAVE;  // readings per lane and block
 constexpr int FOLD_THREADS = 256;
 constexpr int CFOLD_BLOCKS = 64;
-constexpr int64_t CNT_STREAM = 16 * CNT_BLOCK;  // most readings a chunk streams
-constexpr int CHECK_PER = 8;  // readings a thread checks
+// most readings a chunk streams: where the chunks leave waves idle, more take
+// longer than the search; from CNT_MANY chunks on the streams hide each other's
+// latency and are bound by the readings' bytes (300,000 windows over 30M readings,
+// 6,400 a chunk: 206 us streamed, 286 us searched and read again for the check)
+constexpr int64_t CNT_STREAM = 16 * CNT_BLOCK, CNT_STREAM_MANY = 64 * CNT_BLOCK;
+constexpr int64_t CNT_MANY = 4096;
+constexpr int CHECK_PER = 8;  // readings a thread checks at a time
 constexpr int64_t CHECK_BLOCK = (int64_t)CNT_WAVES * WAVE * CHECK_PER;
+// workgroups that check beside or after chunks that do (most find nothing to do;
+// they take more pieces in turn)
+constexpr int64_t CHECK_MAX_BLOCKS = 4096;
+static_assert(FOLD_THREADS == CNT_WAVES * WAVE, "check_readings in either launch");
 
 __device__ __forceinline__ bool finite(double x) { return fabs(x) < INFINITY; }
 
@@ -133,23 +154,28 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t G)
     return (b < 8 * per) ? (b % 8) * per + b / 8 : b;
 }
 
-// readings [blk CHECK_BLOCK, ...): finite, shifted times rising, counter not
-// falling
-__device__ void check_readings(const CounterParams& p, int64_t blk)
+// readings 0 .. head - 1 and from `tail` on, by nblk workgroups: finite, shifted
+// times rising, counter not falling
+__device__ void check_readings(const CounterParams& p, int64_t blk, int64_t nblk, int64_t head,
+                               int64_t tail)
 {
-    const int64_t j0 = blk * CHECK_BLOCK + threadIdx.x;
+    const int64_t total = head + max(p.n - tail, (int64_t)0);
     constexpr int64_t step = CNT_WAVES * WAVE;
     uint32_t err = 0u;
+    for (int64_t v0 = blk * CHECK_BLOCK; v0 < total; v0 += nblk * CHECK_BLOCK) {
 #pragma unroll
-    for (int r = 0; r < CHECK_PER; ++r) {
-        const int64_t j = min(j0 + r * step, p.n - 1);  // (extra lanes repeat the last)
-        const int64_t before = max(j - 1, (int64_t)0);
-        const double t = p.t[j], c = p.C[j];
-        const double u = t - p.delay, ub = p.t[before] - p.delay, cb = p.C[before];
-        const bool first = (j == 0);
-        const bool ok_t = finite(t) && finite(u) && (first || ub < u);
-        const bool ok_c = finite(c) && (first || cb <= c);
-        err |= (ok_t ? 0u : ERR_TIMESTAMPS) | (ok_c ? 0u : ERR_COUNTER);
+        for (int r = 0; r < CHECK_PER; ++r) {
+            // (extra lanes repeat the last)
+            const int64_t v = min(v0 + threadIdx.x + r * step, total - 1);
+            const int64_t j = v < head ? v : v - head + tail;
+            const int64_t before = max(j - 1, (int64_t)0);
+            const double t = p.t[j], c = p.C[j];
+            const double u = t - p.delay, ub = p.t[before] - p.delay, cb = p.C[before];
+            const bool first = (j == 0);
+            const bool ok_t = finite(t) && finite(u) && (first || ub < u);
+            const bool ok_c = finite(c) && (first || cb <= c);
+            err |= (ok_t ? 0u : ERR_TIMESTAMPS) | (ok_c ? 0u : ERR_COUNTER);
+        }
     }
     const uint32_t any = (__ballot((err & ERR_TIMESTAMPS) != 0u) ? ERR_TIMESTAMPS : 0u) |
                          (__ballot((err & ERR_COUNTER) != 0u) ? ERR_COUNTER : 0u);
@@ -185,7 +211,14 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
     __shared__ double lds_u[CNT_WAVES][CNT_BLOCK + 1];
     __shared__ double lds_c[CNT_WAVES][CNT_BLOCK + 1];
     if ((int64_t)blockIdx.x >= nb_win) {
-        check_readings(p, (int64_t)blockIdx.x - nb_win);
+        // all readings, or those that no chunk owns
+        int64_t head = p.n, tail = p.n;
+        if (p.m > 0 && p.chunks_check) {
+            const double u0 = p.t[0] - p.delay, un = p.t[p.n - 1] - p.delay;
+            head = wave_lower_bound(p, p.s[0], u0, un);
+            tail = wave_lower_bound(p, p.e[p.m - 1], u0, un) + 1;
+        }
+        check_readings(p, (int64_t)blockIdx.x - nb_win, (int64_t)gridDim.x - nb_win, head, tail);
         return;
     }
     const int w = threadIdx.x / WAVE, k = threadIdx.x % WAVE;
@@ -202,10 +235,21 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
     const bool has_next = i0 + CNT_CHUNK < m;
     const double s_next = has_next ? p.s[i0 + CNT_CHUNK] : 0.0;
     const double u0 = p.t[0] - p.delay, un = p.t[n - 1] - p.delay;
-    int64_t Jc = 0, last = -1;  // readings Jc .. last hold the chunk's endpoints
+    // readings Jc .. last hold the chunk's endpoints; Jc .. own - 1 are checked
+    int64_t Jc = 0, last = -1, own = 0;
     if (i0 < m) {
+        const double e_last = p.e[min(i0 + CNT_CHUNK, m) - 1];
+        const bool to_next = p.chunks_check && has_next;
         Jc = wave_lower_bound(p, p.s[i0], u0, un);
-        last = min(wave_lower_bound(p, p.e[min(i0 + CNT_CHUNK, m) - 1], u0, un), n - 1);
+        const int64_t J = wave_lower_bound(p, to_next ? s_next : e_last, u0, un);
+        last = min(J, n - 1);
+        if (p.chunks_check) own = to_next ? J : last + 1;
+        if (p.chunks_check && last - Jc >= p.most) {  // uniform
+            // left to the fold launch
+            if (k == 0) atomicOr(&p.status->n_cand, 1u);
+            own = 0;
+            if (has_next) last = min(wave_lower_bound(p, e_last, u0, un), n - 1);
+        }
     }
 
     uint32_t err = 0u;
@@ -219,7 +263,7 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
 
     Endpoint qs{!live, 0, 0.0, 0.0, 0.0, 0.0}, qe{!live, 0, 0.0, 0.0, 0.0, 0.0};
     double lastu = -INFINITY, lastc = 0.0;
-    if (last - Jc >= CNT_STREAM) {  // uniform
+    if (last - Jc >= p.most) {  // uniform
         if (live) search_window(p, qs, qe, s, e, Jc, last + 1);
         last = Jc - 1;
     }
@@ -253,6 +297,20 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
         // the lanes read each other's slots: keep the compiler from moving
         // those reads above the writes (one wave's LDS operations run in order)
         __builtin_amdgcn_wave_barrier();
+        if (own > b) {  // uniform
+#pragma unroll
+            for (int r = 0; r < PER_LANE; ++r) {
+                const int q = k + WAVE * r;
+                const int64_t j = b + q;
+                if (q < cnt && j < own) {
+                    const double uq = tv[r] - p.delay;
+                    const bool first = (j == 0);
+                    const bool ok_t = finite(tv[r]) && finite(uq) && (first || su[q] < uq);
+                    const bool ok_c = finite(cv[r]) && (first || sc[q] <= cv[r]);
+                    err |= (ok_t ? 0u : ERR_TIMESTAMPS) | (ok_c ? 0u : ERR_COUNTER);
+                }
+            }
+        }
         const double ulast = su[cnt];
         resolve(qs, s, b, cnt, ulast, su, sc);
         resolve(qe, e, b, cnt, ulast, su, sc);
@@ -279,15 +337,31 @@ __global__ __launch_bounds__(CNT_WAVES * WAVE) void k_counter(const CounterParam
     const int clipped = count_true(live && (s < u0 || e > un));
 #pragma unroll
     for (int off = WAVE / 2; off > 0; off >>= 1) inc += __shfl_xor(inc, off);
-    const uint32_t any = __ballot((err & ERR_INTERVAL) != 0u) ? ERR_INTERVAL : 0u;
+    const uint32_t any = (__ballot((err & ERR_TIMESTAMPS) != 0u) ? ERR_TIMESTAMPS : 0u) |
+                         (__ballot((err & ERR_COUNTER) != 0u) ? ERR_COUNTER : 0u) |
+                         (__ballot((err & ERR_INTERVAL) != 0u) ? ERR_INTERVAL : 0u);
     if (k == 0) {
         p.part[chunk] = make_double2(inc, (double)clipped);
         if (any) atomicOr(&p.status->err, any);
     }
 }
 
-// whole-trace figures from the per-chunk ones, and the clearing of the
-// group-by state that follows
+int64_t check_blocks(const CounterParams& p)
+{
+    const int64_t pieces = (p.n + CHECK_BLOCK - 1) / CHECK_BLOCK;
+    return p.chunks_check ? std::min(pieces, CHECK_MAX_BLOCKS) : pieces;
+}
+
+// how the readings are divided, from the sizes alone (both launches alike)
+CounterParams with_rules(CounterParams p)
+{
+    p.most = p.nchunks < CNT_MANY ? CNT_STREAM : CNT_STREAM_MANY;
+    p.chunks_check = p.validate && p.n <= p.most * p.nchunks ? 1 : 0;
+    return p;
+}
+
+// whole-trace figures from the per-chunk ones, the clearing of the group-by
+// state that follows, and, where a chunk left its readings, the check of all
 __global__ __launch_bounds__(FOLD_THREADS) void k_counter_fold(const CounterParams p,
                                                                int64_t nb_clear)
 {
@@ -326,6 +400,11 @@ __global__ __launch_bounds__(FOLD_THREADS) void k_counter_fold(const CounterPara
         return;
     }
     const int64_t bc = blk - CFOLD_BLOCKS;
+    if (bc >= nb_clear) {
+        if (p.status->n_cand != 0u)
+            check_readings(p, bc - nb_clear, (int64_t)gridDim.x - CFOLD_BLOCKS - nb_clear, p.n, p.n);
+        return;
+    }
     for (int64_t h = bc * FOLD_THREADS + threadIdx.x; h <= (int64_t)p.H;
          h += nb_clear * FOLD_THREADS) {
         reinterpret_cast<ulonglong2*>(p.table)[h] = make_ulonglong2(~0ull, ~0ull);  // empty, no id
@@ -335,12 +414,13 @@ __global__ __launch_bounds__(FOLD_THREADS) void k_counter_fold(const CounterPara
 
 }  // namespace
 
-hipError_t launch_counter(const CounterParams& p, hipStream_t stream, hipEvent_t ev_start,
+hipError_t launch_counter(const CounterParams& params, hipStream_t stream, hipEvent_t ev_start,
                           hipEvent_t ev_stop)
 {
+    const CounterParams p = with_rules(params);
     // workgroups of windows, then (when the input is checked) of readings
     const int64_t nb_win = (p.nchunks + CNT_WAVES - 1) / CNT_WAVES;
-    const int64_t blocks = nb_win + (p.validate ? (p.n + CHECK_BLOCK - 1) / CHECK_BLOCK : 0);
+    const int64_t blocks = nb_win + (p.validate ? check_blocks(p) : 0);
     if (ev_start || ev_stop)
         hipExtLaunchKernelGGL(k_counter, dim3((unsigned)blocks), dim3(CNT_WAVES * WAVE), 0, stream,
                               ev_start, ev_stop, 0, p, nb_win);
@@ -350,12 +430,14 @@ hipError_t launch_counter(const CounterParams& p, hipStream_t stream, hipEvent_t
     return hipGetLastError();
 }
 
-hipError_t launch_counter_fold(const CounterParams& p, hipStream_t stream)
+hipError_t launch_counter_fold(const CounterParams& params, hipStream_t stream)
 {
+    const CounterParams p = with_rules(params);
     int64_t nb_clear = p.table ? ((int64_t)p.H + FOLD_THREADS) / FOLD_THREADS : 0;
     if (nb_clear > 2048) nb_clear = 2048;
-    hipLaunchKernelGGL(k_counter_fold, dim3((unsigned)(CFOLD_BLOCKS + nb_clear)), dim3(FOLD_THREADS),
-                       0, stream, p, nb_clear);
+    const int64_t blocks = CFOLD_BLOCKS + nb_clear + (p.chunks_check ? check_blocks(p) : 0);
+    hipLaunchKernelGGL(k_counter_fold, dim3((unsigned)blocks), dim3(FOLD_THREADS), 0, stream, p,
+                       nb_clear);
     return hipGetLastError();
 }
 

@@ -51,7 +51,7 @@ struct Status {
     uint32_t overflow;    // a key found no free slot
     unsigned long long n_clipped;
     uint32_t n_unique;    // rows of the compacted distinct-key list
-    uint32_t n_cand;      // diff: surviving candidates
+    uint32_t n_cand;      // diff: surviving candidates; counter: readings are left to check
     uint32_t n_join;      // diff: keys present on both sides
     uint32_t n_waste;     // detect: flagged keys judged waste
     double trace_energy;
@@ -190,6 +190,9 @@ struct CounterParams {
     double2* part;        // [nchunks] {sum of window increases, windows clipped}
     Status* status;
     int validate;
+    // set by the launchers: most readings a chunk streams; chunks check theirs
+    int64_t most;
+    int chunks_check;
     // group-by state cleared by the fold kernel (table NULL: none)
     unsigned long long* table;
     uint32_t H;

@@ -218,3 +218,55 @@ def test_bad_reading_anywhere(j):
         with pytest.raises(mag.MagnetonError) as err:
             mag.attribute_counter(g["t"], g["C"], g["s"], g["e"], g["key"], replays=g["reps"])
         assert err.value.code in ((code,) if name == "C" else (code, -7)), (name, j)
+
+
+def _session(kind):
+    """(readings, window starts and ends): windows dense in the middle of the
+    readings; far apart; two dense stretches with a long pause; one; none."""
+    rng = np.random.default_rng(8500)
+    n = {"dense": 4000, "apart": 60_000, "pause": 30_000, "one": 9000, "none": 5000}[kind]
+    t = np.arange(n) * 0.02 + rng.uniform(0.0, 0.01, n)
+
+    def windows(lo, hi, m):
+        cuts = np.sort(rng.uniform(t[lo], t[hi], 2 * m))
+        return cuts[0::2], cuts[1::2]
+
+    parts = {"dense": [(1000, 3000, 1500)], "apart": [(5000, 55_000, 150)],
+             "pause": [(3000, 4000, 200), (25_000, 26_000, 300)], "one": [(4000, 4500, 1)],
+             "none": []}[kind]
+    ws = [windows(*x) for x in parts] or [(np.zeros(0), np.zeros(0))]
+    return t, np.concatenate([w[0] for w in ws]), np.concatenate([w[1] for w in ws])
+
+
+@pytest.mark.parametrize("kind", ["dense", "apart", "pause", "one", "none"])
+def test_every_reading_is_checked(kind):
+    """One bad reading (a time that does not rise, a counter that falls) at a time:
+    at the trace's ends, around the first reading of every chunk of windows and
+    the last window's last one, at the edges of the checked pieces, and anywhere."""
+    import torch
+    import paper_2512_08365_amd as mag
+    t, s, e = _session(kind)
+    n, m = len(t), len(s)
+    rng = np.random.default_rng(n)
+    C = np.cumsum(rng.uniform(0.5, 1.5, n))
+    edges = list(np.searchsorted(t, s[::64])) + list(np.searchsorted(t, e[-1:]))
+    at = {1, 2, n - 2, n - 1} | {int(x + o) for x in edges for o in (-1, 0, 1)} \
+        | {int(x + o) for x in edges[-1:] + edges[:1] for o in (2047, 2048, 2049)} \
+        | {int(x) for x in rng.integers(1, n, 30)}
+    d = {k: torch.from_numpy(v).cuda() for k, v in (("t", t), ("C", C), ("s", s), ("e", e))}
+    key = torch.zeros(m, dtype=torch.int64, device="cuda") if m else None
+    log(f"[counter] every reading: {kind} n={n} m={m} places={len(at)}")
+
+    def call():
+        return mag.attribute_counter(d["t"], d["C"], d["s"], d["e"], key, key_capacity=4)
+
+    call()
+    for j in sorted(x for x in at if 0 < x < n):
+        for name, value, code in (("t", t[j - 1], -5), ("C", C[j - 1] - 1e-6, -13)):
+            keep = float(d[name][j])
+            d[name][j] = value
+            with pytest.raises(mag.MagnetonError) as err:
+                call()
+            assert err.value.code == code, (kind, name, j)
+            d[name][j] = keep
+    call()
