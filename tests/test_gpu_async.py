@@ -1,7 +1,7 @@
 """Asynchronous attributions (MAG_ASYNC) and their status records.
 
 Each asynchronous call keeps a per-thread record of its workspace: the pinned
-buffer its status block is copied into and the stream the copy runs on.  More
+buffer its status block is sent to and the stream the call runs on.  More
 unfinished calls than the records kept when idle (16) must each still deliver
 their own key count, summary and errors; a call finished while another stream
 is current must wait for its own stream; a second call on a workspace whose
@@ -37,15 +37,17 @@ def _same(got, want, label):
     assert abs(got[2]["trace_energy"] - want[2]["trace_energy"]) <= 1e-12 * want[2]["trace_energy"]
 
 
-def test_twenty_outstanding_calls_keep_their_own_status():
+# groupings by one workgroup, and a mix of those with groupings of several launches
+@pytest.mark.parametrize("per_stream", [40, 6_000])
+def test_twenty_outstanding_calls_keep_their_own_status(per_stream):
     import torch
     import paper_2512_08365_amd as mag
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU")
     # different key counts per case, so a status read from another call's
     # record would show up as a wrong n_keys
-    cases = [synth.tiny_case(900 + i, n=4000 + 97 * i, streams=1 + i % 3, per_stream=40 + 7 * i)
-             for i in range(20)]
+    cases = [synth.tiny_case(900 + i, n=4000 + 97 * i, streams=1 + i % 3,
+                             per_stream=per_stream + 7 * i) for i in range(20)]
     for i, c in enumerate(cases):
         c["key"] = (c["key"] % np.uint64(3 + i)).astype(np.uint64)
     devs = [to_gpu(c) for c in cases]
